@@ -10,7 +10,7 @@ Three kinds of call, each over the range of sizes the workloads of this reposito
 
 The FP32 form holds velocities and accelerations in 32 bits and its readers widen them to doubles; they
 are handed on here in the type they are held in (an exact conversion).  Positions stay doubles (they are
-fixed point with a remainder).  FP32 gradients come back in the parameters' own type.
+fixed point with a remainder).  The FP32 form's objective and gradients come back in the parameters' own type.
 
 ``exact`` restates the model in plain torch in 64 bits (on the GPU, where it is affordable).
 """
@@ -47,9 +47,9 @@ def listed():
              reorder=REORDER),
         # P3M electrostatics in place of the direct sums, at both sizes
         dict(name="p3m-65k-f32", kind="step", real=4, n=65536, steps=40, field=128, law="lognormal", mesh_x=128,
-             mesh_yz=128, reorder=REORDER),
+             mesh_yz=64, reorder=REORDER),
         dict(name="p3m-1m-f32", kind="step", real=4, n=1 << 20, steps=100, field=256, law="four", re_tau=300.0,
-             mesh_x=256, mesh_yz=256, reorder=REORDER),
+             mesh_x=256, mesh_yz=128, reorder=REORDER),
         # gradients for a sensitivity study: samples as in the large batch, and a small set of odd ones
         dict(name="adjoint-16x16k-f32", kind="adjoint", real=4, samples=16, lo=16384, hi=16384, steps=30, ckpt=10,
              field=128),
@@ -81,12 +81,12 @@ def draw(rng):
                     reorder=rng.choice([0, REORDER]))
     if kind == "p3m":
         n = _log_int(rng, 10000, 300000)
-        mx, myz = rng.choice([(64, 64), (128, 64), (128, 128)] if n < 60000 else [(128, 128), (256, 128), (128, 256)])
+        mx, myz = rng.choice([(64, 32), (128, 64), (64, 64)] if n < 60000 else [(128, 64), (256, 128), (128, 128)])
         return dict(kind="step", real=4, n=n, steps=rng.randint(10, 40), field=rng.choice([64, 128]),
                     law=rng.choice(["lognormal", "four"]), mesh_x=mx, mesh_yz=myz, reorder=rng.choice([0, REORDER]))
     if kind == "p3m64":
         return dict(kind="step", real=8, n=_log_int(rng, 4000, 40000), steps=rng.randint(4, 10), field=64,
-                    law="lognormal", mesh_x=64, mesh_yz=64)
+                    law="lognormal", mesh_x=64, mesh_yz=32)
     if kind == "adjoint":
         lo = _log_int(rng, 400, 6000)
         steps = rng.randint(4, 14)
@@ -210,7 +210,7 @@ def run(state):
         cs, ha, te = state["inputs"]
         J = DepositionFn.apply(cs, ha, te, sim, state["seed"], case["steps"], case["ckpt"])
         g = torch.autograd.grad(J, [cs, ha], state["weights"])
-        return dict(J=J.detach(), d_charge_scale=g[0], d_hamaker=g[1])
+        return dict(J=J.detach().to(cs.dtype), d_charge_scale=g[0], d_hamaker=g[1])
     sim.step(case["steps"])
     out = sim.read()
     if case["real"] == 4:
