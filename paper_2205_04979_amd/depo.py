@@ -355,10 +355,12 @@ def lf_solve(params: dict, d, q, A, n_wall: int = 800, n_core: int = 800, device
 
     Moves the three arrays to the device, runs ``depo_lf_solve`` on the current stream and copies the result back."""
     import torch
-    d, q, A = (np.ascontiguousarray(np.broadcast_to(np.asarray(a, dtype=np.float64), np.shape(d))).ravel()
-               for a in (d, q, A))
-    n = d.shape[0]
-    dev = [torch.from_numpy(a.copy()).to(device) for a in (d, q, A)]
+    shape = np.shape(d)
+    host = np.empty((3, int(np.prod(shape, dtype=np.int64))))   # one transfer for the three arrays
+    for row, a in zip(host, (d, q, A)):
+        row[:] = np.broadcast_to(np.asarray(a, dtype=np.float64), shape).ravel()
+    n = host.shape[1]
+    dev = torch.from_numpy(host).to(device)
     out = torch.empty(n, dtype=torch.float64, device=device)
     cp = make_params(params)
     st = lib().depo_lf_solve(C.byref(cp), n, *(C.c_void_p(t.data_ptr()) for t in dev), int(n_wall), int(n_core),

@@ -118,3 +118,36 @@ def test_mfmc_with_particle_step_hf_and_eulerian_lf_matches_oracle_pipeline():
     assert np.isclose(res.variance, ref.variance, rtol=1e-9, atol=0)
     assert np.allclose(res.main, ref.main, rtol=1e-8, atol=1e-12)
     assert np.allclose(res.total, ref.total, rtol=1e-8, atol=1e-12)
+
+
+@pytest.mark.parametrize("n_wall,n_core", [(2, 1), (3, 2), (5, 9), (20, 43), (449, 1), (300, 150)])
+def test_lf_short_grids_against_oracle(n_wall, n_core):
+    """Grids shorter than, equal to and just past one chunk of the node waves (28 cells at this batch size, 448
+    nodes per table), a wall part of two nodes and a core of one."""
+    from paper_2205_04979_amd.depo import lf_solve
+    p = physical_params(180.0)
+    d = np.array([0.3e-6, 1.6e-6, 5e-6, 16e-6, 40e-6])
+    q, A = 0.05 * q_max_charge(d), np.full(5, 4e-19)
+    say(f"case: LF grid {n_wall} + {n_core}")
+    g = lf_solve(p, d, q, A, n_wall=n_wall, n_core=n_core)
+    o = np.array([olf.solve(p, *r, n_wall=n_wall, n_core=n_core) for r in zip(d, q, A)])
+    assert np.allclose(g, o, rtol=RTOL, atol=0), np.max(np.abs(g / o - 1))
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 4096, 4097, 8192, 8193, 10001])
+def test_lf_batch_size_does_not_change_a_class(n):
+    """The classes per workgroup follow the batch size (16, 32, 64): every class's value is that of a small
+    batch, bit for bit; classes with invalid inputs in between change nothing."""
+    from paper_2205_04979_amd.depo import lf_solve
+    rng = np.random.default_rng(n)
+    p = physical_params(180.0)
+    d = np.exp(rng.uniform(np.log(0.05e-6), np.log(30e-6), n))
+    q, A = rng.uniform(0, 0.1, n) * q_max_charge(d), rng.uniform(0, 1, n) * 1e-18
+    bad = rng.random(n) < 0.02
+    q = np.where(bad, np.nan, q)
+    say(f"case: LF batch of {n}")
+    g = lf_solve(p, d, q, A, n_wall=40, n_core=30)
+    pick = np.unique(np.concatenate([np.arange(min(n, 40)), np.arange(max(0, n - 40), n), rng.integers(0, n, 60)]))
+    small = np.concatenate([lf_solve(p, d[k], q[k], A[k], n_wall=40, n_core=30) for k in np.array_split(pick, 4) if k.size])
+    assert np.array_equal(np.isnan(g), bad)
+    assert np.array_equal(g[pick], small, equal_nan=True)
