@@ -50,11 +50,13 @@ struct SampleDev {
 // sources are [j0, j0+jcount).
 struct TileDev { int32_t i0, icount, j0, jcount; };
 
-// One work item of the symmetric pair kernel: targets [i0, i0+icount) against
-// sources [j0, j0+jcount) of sample `sample`.  A diagonal item (j0 == i0) forms
-// all ordered pairs of its tile on the target side and applies no reaction.
+// One work item of the symmetric pair kernel: targets [i0, i0+icount) (a tile) against
+// sources [j0, j0+jcount) of sample `sample`, a whole number of rounds of 64 sources (the last
+// one of the tile or of the sample may be short).  A diagonal item (diag != 0: the sources are the
+// target tile's own) forms all ordered pairs on the target side and applies no reaction;
+// the sources of the others come after the tile.
 struct __align__(32) SymItem {
-  int32_t i0, icount, j0, jcount, sample, pad[3];
+  int32_t i0, icount, j0, jcount, sample, diag, pad[2];
 };
 
 // Per-launch constants, all in double; kernels convert to the working type.

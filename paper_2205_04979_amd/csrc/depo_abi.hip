@@ -22,8 +22,9 @@ using namespace depo;
 constexpr int kSymTileMin = 256;       // smallest symmetric pair-kernel item (64 * ipl * waves targets)
 constexpr int kP3mImages = 256;        // x images summed into the P3M Green's function
 constexpr int64_t kMaxItems = 1 << 22; // largest symmetric item list a layout reserves room for (32 B each)
-// FP32 defaults: the symmetric kernel, or the one-sided kernel where the layout has too many items
-const CoulombConfig kDefaultSym{4, 2, 64, true, true};
+constexpr int kSimds = 1024;           // 256 CUs x 4
+// FP32 defaults: the symmetric kernel (default_sym), or the one-sided kernel where the layout has too
+// many items
 const CoulombConfig kDefaultOneSided{1, 8, 32, true};
 
 namespace {
@@ -77,7 +78,7 @@ struct depo_ctx {
   // symmetric pair kernel (FP32): item capacity (for the smallest item size),
   // item counts, per-sample bounds for the fixed-point scale
   int64_t sym_cap = 0;
-  int n_diag = 0, n_off = 0;
+  int n_items = 0;            // items of the current shape
   // P3M electrostatics (configured before the layout; single-sample layouts)
   bool p3m_cfg = false, p3m_use = false, p3m_green = false;
   int p3m_nx = 0, p3m_nc = 0;
@@ -96,7 +97,8 @@ struct depo_ctx {
   std::vector<SampleDev> samples;
   std::vector<depo_sample_params> sp;
   double dmax_all = 0.0;
-  CoulombConfig ccfg = kDefaultSym;
+  CoulombConfig ccfg{4, 1, 64, true, true};
+  bool shape_set = false;     // ccfg was chosen by depo_set_kernel_config, not by the layout
   Phys ph{};
   State<float> sf{};
   State<double> sd{};
@@ -292,29 +294,71 @@ void build_tiles(depo_ctx *ctx, std::vector<TileDev> &tiles) {
   }
 }
 
-// Work items of the symmetric pair kernel for item size T: per sample, the n_t
-// diagonal items, then the n_t (n_t - 1) / 2 items above the diagonal.
-void build_items(const depo_ctx *ctx, int T, std::vector<SymItem> &items, int &n_diag, int &n_off) {
-  std::vector<SymItem> diag, off;
-  for (int s = 0; s < ctx->S; ++s) {
-    const int64_t b = ctx->off[s], n = ctx->off[s + 1] - b;
-    const int64_t nt = (n + T - 1) / T;
-    auto cnt = [&](int64_t I) { return (int32_t)std::min<int64_t>(T, n - I * T); };
-    for (int64_t I = 0; I < nt; ++I) {
-      const int32_t i0 = (int32_t)(b + I * T);
-      diag.push_back(SymItem{i0, cnt(I), i0, cnt(I), s, {0, 0, 0}});
-      for (int64_t J = I + 1; J < nt; ++J)
-        off.push_back(SymItem{i0, cnt(I), (int32_t)(b + J * T), cnt(J), s, {0, 0, 0}});
+// Items of the symmetric kernel for tiles of T targets and `rounds` rounds of 64 sources per item: per
+// tile, the pieces of its own sources (the diagonal) and of all sources after the tile.
+int64_t count_items(const std::vector<int64_t> &off, int64_t T, int64_t rounds) {
+  const int64_t P = 64 * rounds, Pd = std::min(P, T);
+  int64_t total = 0;
+  for (size_t s = 0; s + 1 < off.size(); ++s) {
+    const int64_t n = off[s + 1] - off[s];
+    for (int64_t b = 0; b < n; b += T) {
+      const int64_t own = std::min(T, n - b);
+      total += (own + Pd - 1) / Pd + (n - b - own + P - 1) / P;
     }
   }
-  // costliest items first
+  return total;
+}
+
+// Items of T targets by T sources, the longest that are built.
+int64_t count_tile_items(const std::vector<int64_t> &off, int64_t T) { return count_items(off, T, T / 64); }
+
+// Rounds per item: longer items cost less (staging, the target side's additions), more items fill the
+// chip and level the end of the launch.  Pair sums of single samples, us: 65,536 particles at (4, 1) 766
+// with 4 rounds, 789 with 2 (33 thousand waves with 4); 45,000 393 and 407 (16 thousand); 30,000 214
+// and 205 (7 thousand); 14,000 at (2, 2) 62.7 with 2, 68.4 with 1 (6 thousand waves with 2); 9,000 at
+// (1, 4) 42.9 and 41.5 (4.9 thousand); 3,001 20.9 and 17.9.  So 4 rounds from 12 waves per SIMD on, 2 from 5 on.
+// A layout whose item list would not fit takes whole tiles.
+int sym_rounds(const depo_ctx *ctx, int T, int waves) {
+  auto fits = [&](int r) { return count_items(ctx->off, T, r) <= ctx->sym_cap; };
+  auto per_simd = [&](int r) { return (double)count_items(ctx->off, T, r) * waves / kSimds; };
+  if (!fits(4)) return T / 64;
+  if (per_simd(4) >= 12.0 || !fits(2)) return 4;
+  return per_simd(2) >= 5.0 || !fits(1) ? 2 : 1;
+}
+
+// The symmetric shape of a layout: more targets per lane share a source's load and rotation but make
+// fewer, longer waves.  By the number of 64 x 64 blocks of pairs (c (c + 1) / 2 per sample of c chunks of
+// 64): pair sums of one sample, us, with 1, 2 and 4 targets per lane: 7,000 particles (6 thousand blocks)
+// 30.5, 42.5, 61; 11,000 (15 thousand) 47, 53, 70; 14,000 (24 thousand) 64.8, 62.7, 78.6; 18,000 (40
+// thousand) 96, 93.5, 98.6; 24,000 (70 thousand) 160, 153, 137; 65,536 (524 thousand) 1,084, 1,012, 766.
+// Tiles of 256 targets, or of 1,024 where 256 would make too many items (2^20 particles: 192 ms).
+CoulombConfig default_sym(const std::vector<int64_t> &off) {
+  if (count_tile_items(off, 256) > kMaxItems) return CoulombConfig{4, 4, 64, true, true};
+  const int64_t blocks = count_items(off, 64, 1);
+  if (blocks <= 20000) return CoulombConfig{1, 4, 64, true, true};
+  if (blocks <= 55000) return CoulombConfig{2, 2, 64, true, true};
+  return CoulombConfig{4, 1, 64, true, true};
+}
+
+// Work items of the symmetric pair kernel, the diagonal ones first, each kind by cost.
+void build_items(const depo_ctx *ctx, int T, int rounds, std::vector<SymItem> &items) {
+  std::vector<SymItem> diag, off;
+  const int64_t P = 64 * (int64_t)rounds, Pd = std::min<int64_t>(P, T);
+  for (int s = 0; s < ctx->S; ++s) {
+    const int64_t e = ctx->off[s + 1];
+    for (int64_t b = ctx->off[s]; b < e; b += T) {
+      const int64_t own = std::min<int64_t>(T, e - b);
+      for (int64_t p = 0; p < own; p += Pd)
+        diag.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)(b + p), (int32_t)std::min(Pd, own - p), s, 1, {0, 0}});
+      for (int64_t j = b + own; j < e; j += P)
+        off.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)j, (int32_t)std::min(P, e - j), s, 0, {0, 0}});
+    }
+  }
   auto by_cost = [](const SymItem &a, const SymItem &c) {
     return (int64_t)a.icount * a.jcount > (int64_t)c.icount * c.jcount;
   };
   std::stable_sort(diag.begin(), diag.end(), by_cost);
   std::stable_sort(off.begin(), off.end(), by_cost);
-  n_diag = (int)diag.size();
-  n_off = (int)off.size();
   items = diag;
   items.insert(items.end(), off.begin(), off.end());
 }
@@ -322,8 +366,10 @@ void build_items(const depo_ctx *ctx, int T, std::vector<SymItem> &items, int &n
 // Upload the symmetric work items for the current configuration.
 depo_status upload_items(depo_ctx *ctx) {
   std::vector<SymItem> items;
-  build_items(ctx, coulomb_sym_tile(ctx->ccfg), items, ctx->n_diag, ctx->n_off);
+  const int T = coulomb_sym_tile(ctx->ccfg);
+  build_items(ctx, T, sym_rounds(ctx, T, ctx->ccfg.waves), items);
   if ((int64_t)items.size() > ctx->sym_cap) return ctx->fail(DEPO_E_CAPACITY, "symmetric item list exceeds capacity");
+  ctx->n_items = (int)items.size();
   if (!items.empty()) HIP_TRY(hipMemcpy(ctx->sf.items, items.data(), items.size() * sizeof(SymItem), hipMemcpyHostToDevice));
   return DEPO_OK;
 }
@@ -372,16 +418,6 @@ depo_status upload_fx_scale(depo_ctx *ctx, hipStream_t stream) {
 
 bool short_range_on(const depo_ctx *ctx) { return (ctx->p.flags & (DEPO_COLLIDE | DEPO_VDW)) != 0; }
 
-// Items of the symmetric kernel for item size T: n_t (n_t + 1) / 2 per sample.
-int64_t count_items(const std::vector<int64_t> &off, int64_t T) {
-  int64_t total = 0;
-  for (size_t s = 0; s + 1 < off.size(); ++s) {
-    const int64_t nt = (off[s + 1] - off[s] + T - 1) / T;
-    total += nt * (nt + 1) / 2;
-  }
-  return total;
-}
-
 // Returns the k_finish mode bit that the pair sums need: with defer_finish, the symmetric pair
 // kernel leaves its fixed-point accumulators to k_finish (F_PAIR_SUMS), one pass fewer per step.
 template <class Real> int enqueue_coulomb(depo_ctx *ctx, hipStream_t s, bool defer_finish = false) {
@@ -392,7 +428,7 @@ template <class Real> int enqueue_coulomb(depo_ctx *ctx, hipStream_t s, bool def
   }
   if constexpr (std::is_same<Real, float>::value) {
     if (ctx->ccfg.symmetric) {
-      launch_coulomb_sym(ctx->sf, ctx->ph, ctx->n_diag, ctx->n_off, ctx->ccfg, s, defer_finish);
+      launch_coulomb_sym(ctx->sf, ctx->ph, ctx->n_items, ctx->ccfg, s, defer_finish);
       return defer_finish ? F_PAIR_SUMS : 0;
     }
   }
@@ -1100,7 +1136,7 @@ template <class Real> depo_status do_adjoint_backward(depo_ctx *ctx, const doubl
       if (coul) {
         if constexpr (std::is_same<Real, float>::value) {
           if (ctx->ccfg.symmetric)
-            launch_coulomb_vjp_sym(ctx->sf, ph, pl.ad, ctx->n_diag, ctx->n_off, ctx->ccfg, s);
+            launch_coulomb_vjp_sym(ctx->sf, ph, pl.ad, ctx->n_items, ctx->ccfg, s);
           else
             launch_coulomb_vjp<Real>(st, ph, pl.ad, ctx->n_tiles, s);
         } else {
@@ -1248,10 +1284,13 @@ depo_status depo_set_layout(depo_ctx *ctx, int32_t n_samples, const int64_t *off
   ctx->sym_cap = 0;
   if (!ctx->fp64()) {
     for (int64_t T = kSymTileMin; T <= 1024 && ctx->sym_cap == 0; T *= 2) {
-      const int64_t k = count_items(ctx->off, T);
+      const int64_t k = count_tile_items(ctx->off, T);
       if (k <= kMaxItems) ctx->sym_cap = k;
     }
-    if (ctx->ccfg.symmetric && count_items(ctx->off, coulomb_sym_tile(ctx->ccfg)) > ctx->sym_cap)
+    // small layouts: room for items of one round (sym_rounds)
+    ctx->sym_cap = std::max<int64_t>(ctx->sym_cap, std::min<int64_t>(count_items(ctx->off, kSymTileMin, 1), 1 << 18));
+    if (!ctx->shape_set) ctx->ccfg = default_sym(ctx->off);
+    if (ctx->ccfg.symmetric && count_tile_items(ctx->off, coulomb_sym_tile(ctx->ccfg)) > ctx->sym_cap)
       ctx->ccfg = kDefaultOneSided;
   }
   if (ctx->p3m_cfg) {
@@ -1393,13 +1432,14 @@ depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int3
                        waves, block);
     if (coulomb_sym_tile(c) < kSymTileMin)
       return ctx->fail(DEPO_E_INVALID, "symmetric items must hold at least %d targets", kSymTileMin);
-    if (ctx->has_layout && count_items(ctx->off, coulomb_sym_tile(c)) > ctx->sym_cap)
+    if (ctx->has_layout && count_tile_items(ctx->off, coulomb_sym_tile(c)) > ctx->sym_cap)
       return ctx->fail(DEPO_E_INVALID, "too many symmetric work items for this layout; use larger items");
   } else if (!coulomb_config_supported(ctx->p.real_bytes, c)) {
     return ctx->fail(DEPO_E_INVALID, "unsupported pair-kernel configuration (%d, %d, %d, %d)", targets_per_lane, waves,
                      block, mode);
   }
   ctx->ccfg = c;
+  ctx->shape_set = true;
   ctx->p3m_use = false;
   ctx->use_graph = use_graph != 0;
   ctx->drop_graph();

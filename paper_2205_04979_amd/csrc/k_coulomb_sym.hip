@@ -2,16 +2,18 @@
 // FP32 form: every unordered pair of a sample is evaluated once and its force
 // is applied to both particles (F_ji = -F_ij, Newton's third law).
 //
-// The pair matrix of a sample is cut into T x T items (T = 64 IPL W).  An item
-// (I, J), I < J, pairs the targets of tile I (IPL per lane, 64 IPL per wave)
-// with the sources of tile J; a diagonal item (I, I) forms all ordered pairs of
-// its tile on the target side only.  Per pair the body is the point-charge form
-// r / (|r|^2 + 1)^(3/2) (one rsq); any round of sources that holds a pair
-// closer than the largest diameter (wave-uniform ballot) is recomputed with the
-// exact overlap clamp r / (|r| max(|r|, d_ij)^2).
+// The pair matrix of a sample is cut into items of T targets (a tile, T = 64 IPL W:
+// IPL per lane, 64 IPL per wave) by a whole number of rounds of 64 sources: all
+// sources after the tile, in equal pieces, and the tile's own (diagonal items,
+// which form all ordered pairs on the target side only).  The number of rounds
+// per item is the layout's (few for small ones: an item is the unit that spreads
+// over the chip; 3,001 particles 132 -> 18 us per evaluation).  Per pair the body
+// is the point-charge form r / (|r|^2 + 1)^(3/2) (one rsq); any round of sources
+// that holds a pair closer than the largest diameter (wave-uniform ballot) is
+// recomputed with the exact overlap clamp r / (|r| max(|r|, d_ij)^2).
 //
-// Ring schedule: the item's source tile is staged in LDS; a wave takes the
-// sources 64 at a time (a round), one per lane, and in step t of a round lane l
+// Ring schedule: sources are staged in LDS, four rounds at a time; a wave takes
+// them 64 at a time (a round), one per lane, and in step t of a round lane l
 // pairs its targets with source (l + t) mod 64, read from LDS (each round is
 // stored twice in a row, so that entry l + t needs no wrap-around).  The reaction
 // accumulated for a source travels with it: after each step the three
@@ -39,6 +41,7 @@ namespace {
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
+constexpr int kStage = 4;          // rounds of sources held in LDS at a time (a power of two)
 constexpr int kWaveRol1 = 0x134;   // lane l receives the value of lane (l + 1) mod 64
 
 __device__ __forceinline__ void fx_add(unsigned long long *acc, int64_t i, double v, double scale) {
@@ -52,25 +55,107 @@ template <bool INTREC> __device__ __forceinline__ float rdiff(float a, float b) 
   else return a - b;
 }
 
+// One round (64 ring steps) of four targets per lane and float records, in machine code.  What
+// bounds the kernel is the rate at which a SIMD issues vector instructions (79 per step and four
+// pairs).  A three-operand instruction whose registers are all odd or all even takes two issue slots
+// instead of one (measured: 4.5 against 2.25 cycles for v_fmac_f32); left to the compiler a sixth of the
+// accumulations did, and the copies it added made 83 instructions.  Here every accumulator sits in an
+// odd register and every weight in an even one, each stage runs over the four targets before the
+// next, and the next source record is on its way while one is evaluated.
+// The reciprocal roots and the lane rotations hold back the wave that issues them, and waves in step with
+// each other wait together; they are issued at a raised wave priority, so that the other waves'
+// multiply-adds fill in behind them (without it: 11 % slower).
+// Measured (pair sums per step, compiled body with an item per two tiles -> this one): 65,536 particles
+// 893 -> 762 us; ten samples of 2,048 to 32,768 740 -> 635 us; 2^20 particles 213 -> 192.5 ms, 70 TFLOP/s
+// at 25 operations per unordered pair.
+// addr: LDS byte address of the lane's record of step 0 (16-byte records); s: sums of the target
+// side, r: reactions, both set; returns the lanes in which some pair was near.
+__device__ __forceinline__ uint64_t ring_round4(uint32_t addr, const uint32_t (&x)[4], const float (&y)[4],
+                                                const float (&z)[4], const float (&q)[4], float near2,
+                                                float (&sx)[4], float (&sy)[4], float (&sz)[4], float &rx, float &ry,
+                                                float &rz) {
+  uint64_t mask;
+  uint32_t cnt;
+  // registers: sums v33..v55 and reactions v57, v59, v61 (odd); weights v32..v46 (even); dx v48..v54,
+  // dy v56..v62 (even), dz v63..v66; |r|^2 + 1, then its reciprocal root v67..v70; records v72..v79
+#define DEPO_RING_STEP(X, Y, Z, Q)                                                                     \
+  "v_sub_u32 v48, %[x0], " X "\n v_sub_u32 v50, %[x1], " X "\n"                                        \
+  "v_sub_u32 v52, %[x2], " X "\n v_sub_u32 v54, %[x3], " X "\n"                                        \
+  "v_sub_f32 v63, %[z0], " Z "\n v_sub_f32 v64, %[z1], " Z "\n"                                        \
+  "v_sub_f32 v65, %[z2], " Z "\n v_sub_f32 v66, %[z3], " Z "\n"                                        \
+  "v_cvt_f32_i32 v48, v48\n v_sub_f32 v56, %[y0], " Y "\n v_cvt_f32_i32 v50, v50\n"                    \
+  "v_sub_f32 v58, %[y1], " Y "\n v_cvt_f32_i32 v52, v52\n v_sub_f32 v60, %[y2], " Y "\n"               \
+  "v_cvt_f32_i32 v54, v54\n v_sub_f32 v62, %[y3], " Y "\n"                                            \
+  "v_fma_f32 v67, v63, v63, 1.0\n v_fma_f32 v68, v64, v64, 1.0\n"                                     \
+  "v_fma_f32 v69, v65, v65, 1.0\n v_fma_f32 v70, v66, v66, 1.0\n"                                     \
+  "v_fmac_f32 v67, v56, v56\n v_fmac_f32 v68, v58, v58\n"                                             \
+  "v_fmac_f32 v69, v60, v60\n v_fmac_f32 v70, v62, v62\n"                                             \
+  "v_fmac_f32 v67, v48, v48\n v_fmac_f32 v68, v50, v50\n"                                             \
+  "v_fmac_f32 v69, v52, v52\n v_fmac_f32 v70, v54, v54\n"                                             \
+  "v_cmp_gt_f32 vcc, %[near2], v67\n s_or_b64 %[mask], %[mask], vcc\n"                                \
+  "v_cmp_gt_f32 vcc, %[near2], v68\n s_or_b64 %[mask], %[mask], vcc\n"                                   \
+  "v_cmp_gt_f32 vcc, %[near2], v69\n s_or_b64 %[mask], %[mask], vcc\n"                                   \
+  "v_cmp_gt_f32 vcc, %[near2], v70\n s_or_b64 %[mask], %[mask], vcc\n"                                   \
+  "s_setprio 1\n v_rsq_f32 v67, v67\n v_rsq_f32 v68, v68\n v_rsq_f32 v69, v69\n v_rsq_f32 v70, v70\n s_setprio 0\n" \
+  "v_mul_f32 v32, v67, v67\n v_mul_f32 v34, v68, v68\n"                                               \
+  "v_mul_f32 v36, v69, v69\n v_mul_f32 v38, v70, v70\n"                                               \
+  "v_mul_f32 v67, v67, v32\n v_mul_f32 v68, v68, v34\n"                                               \
+  "v_mul_f32 v69, v69, v36\n v_mul_f32 v70, v70, v38\n"                                               \
+  "v_mul_f32 v40, %[q0], v67\n v_mul_f32 v42, %[q1], v68\n"                                           \
+  "v_mul_f32 v44, %[q2], v69\n v_mul_f32 v46, %[q3], v70\n"                                           \
+  "v_mul_f32 v32, " Q ", v67\n v_mul_f32 v34, " Q ", v68\n"                                           \
+  "v_mul_f32 v36, " Q ", v69\n v_mul_f32 v38, " Q ", v70\n"                                           \
+  "v_fmac_f32 v57, v40, v48\n v_fmac_f32 v59, v40, v56\n v_fmac_f32 v61, v40, v63\n"                  \
+  "v_fmac_f32 v33, v32, v48\n v_fmac_f32 v35, v32, v56\n v_fmac_f32 v37, v32, v63\n"                  \
+  "v_fmac_f32 v57, v42, v50\n v_fmac_f32 v59, v42, v58\n v_fmac_f32 v61, v42, v64\n"                  \
+  "v_fmac_f32 v39, v34, v50\n v_fmac_f32 v41, v34, v58\n v_fmac_f32 v43, v34, v64\n"                  \
+  "v_fmac_f32 v57, v44, v52\n v_fmac_f32 v59, v44, v60\n v_fmac_f32 v61, v44, v65\n"                  \
+  "v_fmac_f32 v45, v36, v52\n v_fmac_f32 v47, v36, v60\n v_fmac_f32 v49, v36, v65\n"                  \
+  "v_fmac_f32 v57, v46, v54\n v_fmac_f32 v59, v46, v62\n v_fmac_f32 v61, v46, v66\n"                  \
+  "v_fmac_f32 v51, v38, v54\n v_fmac_f32 v53, v38, v62\n v_fmac_f32 v55, v38, v66\n"                  \
+  "s_setprio 1\n v_mov_b32_dpp v57, v57 wave_rol:1 row_mask:0xf bank_mask:0xf\n"                                    \
+  "v_mov_b32_dpp v59, v59 wave_rol:1 row_mask:0xf bank_mask:0xf\n"                                    \
+  "v_mov_b32_dpp v61, v61 wave_rol:1 row_mask:0xf bank_mask:0xf\n s_setprio 0\n"
+#define DEPO_RING_A DEPO_RING_STEP("v72", "v73", "v74", "v75")
+#define DEPO_RING_B DEPO_RING_STEP("v76", "v77", "v78", "v79")
+  // Every load is waited for inside the block (the last one reads entry 64 of the round, which is
+  // stored, and is not used).
+  asm volatile(
+      "s_waitcnt lgkmcnt(0)\n"
+      "ds_read_b128 v[72:75], %[addr]\n"
+      "s_mov_b64 %[mask], 0\n"
+      "s_mov_b32 %[cnt], 16\n"
+      "v_mov_b32 v33, 0\n v_mov_b32 v35, 0\n v_mov_b32 v37, 0\n v_mov_b32 v39, 0\n v_mov_b32 v41, 0\n"
+      "v_mov_b32 v43, 0\n v_mov_b32 v45, 0\n v_mov_b32 v47, 0\n v_mov_b32 v49, 0\n v_mov_b32 v51, 0\n"
+      "v_mov_b32 v53, 0\n v_mov_b32 v55, 0\n v_mov_b32 v57, 0\n v_mov_b32 v59, 0\n v_mov_b32 v61, 0\n"
+      ".Lring%=:\n"
+      "ds_read_b128 v[76:79], %[addr] offset:16\n s_waitcnt lgkmcnt(1)\n" DEPO_RING_A
+      "ds_read_b128 v[72:75], %[addr] offset:32\n s_waitcnt lgkmcnt(1)\n" DEPO_RING_B
+      "ds_read_b128 v[76:79], %[addr] offset:48\n s_waitcnt lgkmcnt(1)\n" DEPO_RING_A
+      "ds_read_b128 v[72:75], %[addr] offset:64\n v_add_u32 %[addr], 64, %[addr]\n s_waitcnt lgkmcnt(1)\n" DEPO_RING_B
+      "s_sub_u32 %[cnt], %[cnt], 1\n"
+      "s_cmp_lg_u32 %[cnt], 0\n"
+      "s_cbranch_scc1 .Lring%=\n"
+      "s_waitcnt lgkmcnt(0)\n"
+      : [mask] "=&s"(mask), [cnt] "=&s"(cnt), [addr] "+v"(addr), "=&{v33}"(sx[0]), "=&{v35}"(sy[0]), "=&{v37}"(sz[0]),
+        "=&{v39}"(sx[1]), "=&{v41}"(sy[1]), "=&{v43}"(sz[1]), "=&{v45}"(sx[2]), "=&{v47}"(sy[2]), "=&{v49}"(sz[2]),
+        "=&{v51}"(sx[3]), "=&{v53}"(sy[3]), "=&{v55}"(sz[3]), "=&{v57}"(rx), "=&{v59}"(ry), "=&{v61}"(rz)
+      : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [y0] "v"(y[0]), [y1] "v"(y[1]),
+        [y2] "v"(y[2]), [y3] "v"(y[3]), [z0] "v"(z[0]), [z1] "v"(z[1]), [z2] "v"(z[2]), [z3] "v"(z[3]),
+        [q0] "v"(q[0]), [q1] "v"(q[1]), [q2] "v"(q[2]), [q3] "v"(q[3]), [near2] "s"(near2)
+      : "v32", "v34", "v36", "v38", "v40", "v42", "v44", "v46", "v48", "v50", "v52", "v54", "v56", "v58", "v60", "v62",
+        "v63", "v64", "v65", "v66", "v67", "v68", "v69", "v70", "v72", "v73", "v74", "v75", "v76", "v77", "v78",
+        "v79", "vcc", "scc", "memory");
+  return mask;
+}
+
 template <int IPL, int W, bool REACT, bool INTREC>
 __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *__restrict__ js,
                                           const float *__restrict__ jr, double scale,
                                           unsigned long long *__restrict__ accx, unsigned long long *__restrict__ accy,
-                                          unsigned long long *__restrict__ accz, float near2, JSrc<float> *src,
-                                          float *srad) {
+                                          unsigned long long *__restrict__ accz, float near2, JSrc<float> *src) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
-  // stage the source tile, each round of 64 twice in a row (entry 128 r + k holds source
-  // 64 r + (k mod 64)); charge 0 beyond jcount: padding of the last round
-  for (int e = threadIdx.x; e < 2 * 64 * IPL * W; e += 64 * W) {
-    const int jj = (e >> 7) * 64 + (e & 63);
-    const bool has = jj < it.jcount;
-    JSrc<float> r = js[it.j0 + (has ? jj : 0)];
-    if (!has) r.q = 0.0f;
-    src[e] = r;
-    srad[e] = jr[it.j0 + (has ? jj : 0)];
-  }
 
   uint32_t xi[IPL];
   float yi[IPL], zi[IPL], qi[IPL], ri[IPL];
@@ -88,10 +173,23 @@ __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *
   float hx[IPL], hy[IPL], hz[IPL], cx[IPL], cy[IPL], cz[IPL];
 #pragma unroll
   for (int k = 0; k < IPL; ++k) hx[k] = hy[k] = hz[k] = cx[k] = cy[k] = cz[k] = 0.0f;
-  __syncthreads();
 
   for (int jb = 0; jb < it.jcount; jb += 64) {
-    const JSrc<float> *rs = src + 2 * jb + lane;
+    if ((jb & (64 * kStage - 1)) == 0) {
+      // stage the next kStage rounds, each twice in a row (entry 128 r + k holds source
+      // 64 r + (k mod 64)); charge 0 beyond jcount: padding of the last round
+      const int left = it.jcount - jb, n = 128 * min(kStage, (left + 63) >> 6);
+      __syncthreads();
+      for (int e = threadIdx.x; e < n; e += 64 * W) {
+        const int jj = (e >> 7) * 64 + (e & 63);
+        const bool has = jj < left;
+        JSrc<float> r = js[it.j0 + jb + (has ? jj : 0)];
+        if (!has) r.q = 0.0f;
+        src[e] = r;
+      }
+      __syncthreads();
+    }
+    const JSrc<float> *rs = src + 2 * (jb & (64 * kStage - 1)) + lane;
     float sx[IPL], sy[IPL], sz[IPL];
     float rx = 0.0f, ry = 0.0f, rz = 0.0f;   // reaction of the source now in this lane
 #pragma unroll
@@ -128,11 +226,16 @@ __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *
         rz = dpp<kWaveRol1>(rz);
       }
     };
-    if constexpr (REACT) {
+    if constexpr (REACT && IPL == 4 && !INTREC) {
+      // LDS addresses are the low 32 bits of a generic pointer into it
+      nearmask = ring_round4((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) JSrc<float> *)rs, xi, yi, zi,
+                             qi, near2, sx, sy, sz, rx, ry, rz);
+    } else if constexpr (REACT) {
 #pragma unroll 4
       for (int t = 0; t < 64; ++t) step(t, -1);
     } else {
-      const int kself = (jb - w * 64 * IPL) >> 6;   // wave-uniform; outside [0, IPL) when no self pair
+      // wave-uniform; outside [0, IPL) when no self pair
+      const int kself = (it.j0 - it.i0 + jb - w * 64 * IPL) >> 6;
       step(0, kself);
 #pragma unroll 3
       for (int t = 1; t < 64; ++t) step(t, -1);
@@ -143,9 +246,9 @@ __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *
       for (int k = 0; k < IPL; ++k) sx[k] = sy[k] = sz[k] = 0.0f;
       rx = ry = rz = 0.0f;
       for (int t = 0; t < 64; ++t) {
-        const int e = 2 * jb + lane + t;
-        const JSrc<float> s = src[e];
-        const float rj = srad[e];
+        const JSrc<float> s = rs[t];
+        const int jj = jb + ((lane + t) & 63);   // radii come from memory: this path is rare
+        const float rj = jr[it.j0 + (jj < it.jcount ? jj : 0)];
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
           const float dx = sdiff(xi[k], s.x);
@@ -210,15 +313,13 @@ __global__ __launch_bounds__(64 * W) void k_coulomb_sym(const SymItem *__restric
                                                         unsigned long long *__restrict__ accx,
                                                         unsigned long long *__restrict__ accy,
                                                         unsigned long long *__restrict__ accz, float near2) {
-  constexpr int T = 64 * IPL * W;
-  __shared__ JSrc<float> src[2 * T];
-  __shared__ float srad[2 * T];
+  __shared__ JSrc<float> src[128 * kStage];
   const SymItem it = items[blockIdx.x];
   const double scale = fx_scale[it.sample];
-  if (it.j0 == it.i0)
-    ring_item<IPL, W, false, INTREC>(it, js, jr, scale, accx, accy, accz, near2, src, srad);
+  if (it.diag)
+    ring_item<IPL, W, false, INTREC>(it, js, jr, scale, accx, accy, accz, near2, src);
   else
-    ring_item<IPL, W, true, INTREC>(it, js, jr, scale, accx, accy, accz, near2, src, srad);
+    ring_item<IPL, W, true, INTREC>(it, js, jr, scale, accx, accy, accz, near2, src);
 }
 
 // Fixed-point totals back to pair sums; the accumulators are cleared for the next evaluation.
@@ -241,7 +342,7 @@ __global__ __launch_bounds__(256) void k_pair_finish(int32_t N, const int32_t *_
 
 }  // namespace
 
-// (targets per lane, waves); T = 64 IPL W targets per item, rounds of 64 sources
+// (targets per lane, waves); T = 64 IPL W targets per tile, rounds of 64 sources
 #define DEPO_COULOMB_SYM_CASES(X) X(1, 4) X(1, 8) X(2, 2) X(2, 4) X(4, 1) X(4, 2) X(4, 4) X(8, 1)
 
 int coulomb_sym_tile(const CoulombConfig &cfg) { return 64 * cfg.ipl * cfg.waves; }
@@ -255,10 +356,9 @@ bool coulomb_sym_supported(const CoulombConfig &cfg) {
   return false;
 }
 
-void launch_coulomb_sym(const State<float> &st, const Phys &ph, int n_diag, int n_off, const CoulombConfig &cfg,
+void launch_coulomb_sym(const State<float> &st, const Phys &ph, int n_items, const CoulombConfig &cfg,
                         hipStream_t s, bool defer_finish) {
   const float near2 = (float)ph.near2;
-  const int n_items = n_diag + n_off;
 #define X(I, W)                                                                                              \
   if (n_items > 0 && cfg.ipl == I && cfg.waves == W) {                                                       \
     if (cfg.int_rec)                                                                                         \

@@ -10,8 +10,8 @@
 // exactly the negative: each unordered pair is evaluated once and its term is
 // added to i and subtracted from j, as in the forward kernel.
 //
-// Schedule (same as the forward): the source tile of an item is staged in LDS,
-// each round of 64 twice in a row; in step t lane l pairs its IPL targets with
+// Schedule (same as the forward): the sources of an item are staged in LDS,
+// four rounds of 64 at a time, each twice in a row; in step t lane l pairs its IPL targets with
 // source (l + t) mod 64 and the three reaction sums travel with the source (DPP
 // wave rotate), so after 64 steps they are back in the source's own lane.
 // Per pair the fast body uses the point-charge form with |r|^2 + 1 (one rsq);
@@ -37,6 +37,7 @@ namespace {
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
+constexpr int kStage = 4;          // rounds of sources held in LDS at a time (a power of two)
 constexpr int kWaveRol1 = 0x134;   // lane l receives the value of lane (l + 1) mod 64
 
 __device__ __forceinline__ void dadd(double *acc, int64_t i, double v) { unsafeAtomicAdd(acc + i, v); }
@@ -45,20 +46,9 @@ template <int IPL, int W, bool REACT>
 __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *__restrict__ rec,
                                          const float *__restrict__ jr, double *__restrict__ ax,
                                          double *__restrict__ ay, double *__restrict__ az, float near2,
-                                         JAdj<float> *src, float *srad) {
+                                         JAdj<float> *src) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-
-  // stage the source tile (entry 128 r + k holds source 64 r + (k mod 64)); padding of the
-  // last round has q = 0 and b = 0, so p = 0 and it contributes nothing to either side
-  for (int e = threadIdx.x; e < 2 * 64 * IPL * W; e += 64 * W) {
-    const int jj = (e >> 7) * 64 + (e & 63);
-    const bool has = jj < it.jcount;
-    JAdj<float> r = rec[it.j0 + (has ? jj : 0)];
-    if (!has) r.q = r.bx = r.by = r.bz = 0.0f;
-    src[e] = r;
-    srad[e] = jr[it.j0 + (has ? jj : 0)];
-  }
 
   uint32_t xi[IPL];
   float yi[IPL], zi[IPL], qi[IPL], bx[IPL], by[IPL], bz[IPL], ri[IPL];
@@ -80,10 +70,23 @@ __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *_
   double hx[IPL], hy[IPL], hz[IPL];
 #pragma unroll
   for (int k = 0; k < IPL; ++k) hx[k] = hy[k] = hz[k] = 0.0;
-  __syncthreads();
 
   for (int jb = 0; jb < it.jcount; jb += 64) {
-    const JAdj<float> *rs = src + 2 * jb + lane;
+    if ((jb & (64 * kStage - 1)) == 0) {
+      // stage the next kStage rounds (entry 128 r + k holds source 64 r + (k mod 64)); padding of the
+      // last round has q = 0 and b = 0, so p = 0 and it contributes nothing to either side
+      const int left = it.jcount - jb, n = 128 * min(kStage, (left + 63) >> 6);
+      __syncthreads();
+      for (int e = threadIdx.x; e < n; e += 64 * W) {
+        const int jj = (e >> 7) * 64 + (e & 63);
+        const bool has = jj < left;
+        JAdj<float> r = rec[it.j0 + jb + (has ? jj : 0)];
+        if (!has) r.q = r.bx = r.by = r.bz = 0.0f;
+        src[e] = r;
+      }
+      __syncthreads();
+    }
+    const JAdj<float> *rs = src + 2 * (jb & (64 * kStage - 1)) + lane;
     float sx[IPL], sy[IPL], sz[IPL];
     float rx = 0.0f, ry = 0.0f, rz = 0.0f;   // reaction of the source now in this lane
 #pragma unroll
@@ -122,7 +125,7 @@ __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *_
         rz = dpp<kWaveRol1>(rz);
       }
     };
-    const int kself = REACT ? -1 : (jb - w * 64 * IPL) >> 6;   // wave-uniform
+    const int kself = REACT ? -1 : (it.j0 - it.i0 + jb - w * 64 * IPL) >> 6;   // wave-uniform
     step(0, kself);
 #pragma unroll 3
     for (int t = 1; t < 64; ++t) step(t, -1);
@@ -132,9 +135,9 @@ __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *_
       for (int k = 0; k < IPL; ++k) sx[k] = sy[k] = sz[k] = 0.0f;
       rx = ry = rz = 0.0f;
       for (int t = 0; t < 64; ++t) {
-        const int e = 2 * jb + lane + t;
-        const JAdj<float> s = src[e];
-        const float rj = srad[e];
+        const JAdj<float> s = rs[t];
+        const int jj = jb + ((lane + t) & 63);
+        const float rj = jr[it.j0 + (jj < it.jcount ? jj : 0)];
 #pragma unroll
         for (int k = 0; k < IPL; ++k) {
           const float dx = sdiff(xi[k], s.x);
@@ -199,14 +202,12 @@ __global__ __launch_bounds__(64 * W) void k_coulomb_vjp_sym(const SymItem *__res
                                                             const float *__restrict__ jr, double *__restrict__ ax,
                                                             double *__restrict__ ay, double *__restrict__ az,
                                                             float near2) {
-  constexpr int T = 64 * IPL * W;
-  __shared__ JAdj<float> src[2 * T];
-  __shared__ float srad[2 * T];
+  __shared__ JAdj<float> src[128 * kStage];
   const SymItem it = items[blockIdx.x];
-  if (it.j0 == it.i0)
-    vjp_item<IPL, W, false>(it, rec, jr, ax, ay, az, near2, src, srad);
+  if (it.diag)
+    vjp_item<IPL, W, false>(it, rec, jr, ax, ay, az, near2, src);
   else
-    vjp_item<IPL, W, true>(it, rec, jr, ax, ay, az, near2, src, srad);
+    vjp_item<IPL, W, true>(it, rec, jr, ax, ay, az, near2, src);
 }
 
 // Totals (in units of the x quantum) to x_bar contributions; the accumulators are cleared.
@@ -226,22 +227,27 @@ __global__ __launch_bounds__(256) void k_vjp_finish(int32_t N, float inv_ux, dou
 
 }  // namespace
 
-#define DEPO_VJP_SYM_CASES(X) X(1, 4) X(1, 8) X(2, 2) X(2, 4) X(4, 1) X(4, 2) X(4, 4) X(8, 1)
-
-void launch_coulomb_vjp_sym(const State<float> &st, const Phys &ph, const AdjState<float> &ad, int n_diag, int n_off,
+void launch_coulomb_vjp_sym(const State<float> &st, const Phys &ph, const AdjState<float> &ad, int n_items,
                             const CoulombConfig &cfg, hipStream_t s) {
   // the forward's fixed-point accumulators are zero between evaluations; the same memory
   // holds the FP64 sums here and is zero again after k_vjp_finish
   double *ax = reinterpret_cast<double *>(st.accx);
   double *ay = reinterpret_cast<double *>(st.accy);
   double *az = reinterpret_cast<double *>(st.accz);
-  const int n_items = n_diag + n_off;
-#define X(I, W)                                                                                            \
-  if (n_items > 0 && cfg.ipl == I && cfg.waves == W)                                                       \
-    hipLaunchKernelGGL((k_coulomb_vjp_sym<I, W>), dim3(n_items), dim3(64 * W), 0, s, st.items, ad.rec,     \
-                       st.jr, ax, ay, az, (float)ph.near2);
-  DEPO_VJP_SYM_CASES(X)
-#undef X
+  // The forward's items fix the tile; its targets per lane are the adjoint's own choice.  With 32
+  // instructions per pair the source's load and rotation weigh little and the waves in flight more: two
+  // targets per lane (45,000 particles: 897 us per reverse step, 1,060 with four), one for the small
+  // layouts whose forward takes one (sizes as there).
+  auto go = [&](auto kernel, int threads) {
+    if (n_items > 0)
+      hipLaunchKernelGGL(kernel, dim3(n_items), dim3(threads), 0, s, st.items, ad.rec, st.jr, ax, ay, az,
+                         (float)ph.near2);
+  };
+  switch (coulomb_sym_tile(cfg)) {
+    case 256: cfg.ipl == 1 ? go(k_coulomb_vjp_sym<1, 4>, 256) : go(k_coulomb_vjp_sym<2, 2>, 128); break;
+    case 512: go(k_coulomb_vjp_sym<2, 4>, 256); break;
+    default: go(k_coulomb_vjp_sym<4, 4>, 256); break;   // 1,024
+  }
   if (ph.N > 0)
     hipLaunchKernelGGL(k_vjp_finish, dim3((ph.N + 255) / 256), dim3(256), 0, s, ph.N, (float)ph.inv_ux, ax, ay, az,
                        ad.xc[0], ad.xc[1], ad.xc[2]);

@@ -47,7 +47,7 @@ int coulomb_sym_tile(const CoulombConfig &cfg);   // targets (= sources) per ite
 bool coulomb_sym_supported(const CoulombConfig &cfg);
 // defer_finish: leave the fixed-point accumulators for k_finish (mode F_PAIR_SUMS) instead of
 // converting them with k_pair_finish
-void launch_coulomb_sym(const State<float> &st, const Phys &ph, int n_diag, int n_off, const CoulombConfig &cfg,
+void launch_coulomb_sym(const State<float> &st, const Phys &ph, int n_items, const CoulombConfig &cfg,
                         hipStream_t s, bool defer_finish = false);
 
 // P3M electrostatics (single-sample layouts): mesh geometry, splitting and workspace.

@@ -263,7 +263,7 @@ class Simulation(Context):
                           compensated: Optional[bool] = None):
         """Pair-kernel shape and mode: PAIR_PLAIN, PAIR_KAHAN, PAIR_SYMMETRIC or PAIR_SYMMETRIC_INT (FP32).  ``mode=None`` selects
         the one-sided Kahan mode in FP32 and plain in FP64 (before any call the library runs the symmetric
-        mode, shape (4, 2, 64), in FP32).  ``compensated`` (bool) is accepted in place of ``mode`` for the
+        mode in FP32, its shape chosen by the layout).  ``compensated`` (bool) is accepted in place of ``mode`` for the
         one-sided modes.  The FP32 adjoint uses the symmetric pair adjoint when the mode is symmetric."""
         if mode is None:
             mode = (PAIR_KAHAN if compensated else PAIR_PLAIN) if compensated is not None else (

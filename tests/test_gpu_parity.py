@@ -812,3 +812,45 @@ def test_step_converts_the_pair_sums_like_the_evaluation(use_graph):
     for _ in range(2):
         sim.eval_accel()
         assert np.array_equal(sim.read()["a"], a_step)
+
+
+@pytest.mark.parametrize("sizes", [(1, 63, 64, 65, 255, 256, 257, 511, 513, 1, 2049), (5000,), (11500,), (19000,),
+                                   (22100, 300, 9001)])
+def test_fp32_default_shape_by_layout(sizes):
+    """The layout chooses the symmetric kernel's targets per lane and how its tiles' sources are cut into
+    items: samples at the edges of rounds and tiles, and sizes on either side of each choice, with pairs inside
+    the overlap clamp at the far ends of a sample.  Forces of targets at those edges against the oracle;
+    two runs from one seed agree bitwise."""
+    n = sum(sizes)
+    w = make_workload("single-65k", n=n, field_n=32)
+    f = w.field()
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    sp = np.repeat(w.sample_params[:1], len(sizes), axis=0)
+    p = dict(w.params, collide=False, vdw=False)
+    x = w.x.copy()
+    for b, e in zip(off[:-1], off[1:]):
+        if e - b >= 255:            # overlapping pairs across the sample, and inside its first tile
+            x[e - 1] = x[b] + 0.3 * w.d[b] * np.array([1.0, 0.0, 0.0])
+            x[b + 70] = x[b + 3] + 0.4 * w.d[b] * np.array([1.0, 0.0, 0.0])
+    say("case: default shape, sizes", sizes)
+    sim, _ = seeded_pair(p, f, x, w.d, w.qbase, off, sp, 4, oracle=False)
+    sim.eval_accel()
+    g = sim.read()
+    tg = set()
+    for b, e in zip(off[:-1], off[1:]):
+        tg |= {int(t) for k in (0, 3, 63, 64, 70, 255, 256, 511, 512, e - b - 65, e - b - 64, e - b - 1)
+               for t in [b + k] if b <= t < e}
+        tg |= set(range(int(b), int(e), 97))
+    tg = np.array(sorted(tg))
+    ora = oracle_from_snapshot(p, f, g, w.d, w.qbase, off, sp, g["dep_step"])
+    scale = coulomb_scale(ora, tg)
+    ok = scale > 0                  # a particle alone has no pair force
+    e = force_error(g["a"][tg][ok], ora.accelerations(tg)[ok], scale[ok])
+    say("targets", tg.size, "force error max", e.max(), "median", np.median(e))
+    assert e.max() < 1e-5
+    sim.step(2)
+    a = sim.read()["a"]
+    sim2, _ = seeded_pair(p, f, x, w.d, w.qbase, off, sp, 4, oracle=False)
+    sim2.step(1)
+    sim2.step(1)
+    assert np.array_equal(a, sim2.read()["a"])
