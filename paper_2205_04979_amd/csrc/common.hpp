@@ -77,6 +77,7 @@ struct Phys {
   double g_body[3];
   double E_young, delta_c, acont_coef;
   double soft_eps, soft_rate;     // eps_s = soft_eps d ; dl/dt = sigma(-g/eps_s) * soft_rate
+  int32_t pair_parts;             // pieces of each sample's sources in the FP64 pair kernel
   double near2;                   // (largest diameter / ux)^2: pair-kernel exact-path threshold
 };
 
@@ -111,6 +112,7 @@ struct State {
   TileDev *tiles;
   SymItem *items;                 // symmetric pair-kernel work items (FP32 only)
   double *fx_scale;               // [S] fixed-point units per unit of pair sum, per sample
+  double *part;                   // [pieces][3][N] partial pair sums of the FP64 kernel (pieces > 1)
   unsigned long long *accx, *accy, *accz;  // [N] fixed-point pair-sum accumulators (zero between steps)
   typename Prec<Real>::Vec4 *field;
   int32_t *nstep;
@@ -230,7 +232,11 @@ __device__ __forceinline__ int x_cell(uint64_t x, int n) { return (int)__umul64h
 
 // Signed fixed-point difference a - b converted to the working type (minimum image in x).
 __device__ __forceinline__ float sdiff(uint32_t a, uint32_t b) { return (float)(int32_t)(a - b); }
-__device__ __forceinline__ double sdiff(uint64_t a, uint64_t b) { return (double)(int64_t)(a - b); }
+__device__ __forceinline__ double sdiff(uint64_t a, uint64_t b) {
+  // (double)(int64_t)(a - b) with one rounding, in three instructions instead of the conversion's four
+  const uint64_t d = a - b;
+  return fma((double)(int32_t)(uint32_t)(d >> 32), 0x1p32, (double)(uint32_t)d);
+}
 
 // Centre displacement of particle i from particle j in metres (minimum image in x), its length,
 // and the surface gap |r| - s for the contact distance s = (d_i + d_j)/2, all in FP64 from the
@@ -247,6 +253,16 @@ __device__ __forceinline__ double pair_gap(Pos xi, Pos yi, Pos zi, Pos xj, Pos y
   const double r2 = dx * dx + dy * dy + dz * dz;
   dist = sqrt(r2);
   return (r2 - s * s) / (dist + s);
+}
+
+// Partial pair sums [parts][3][N] of particle i added in the order of the parts.
+__device__ __forceinline__ void sum_parts(const double *__restrict__ part, int parts, int N, int i, double (&s)[3]) {
+  s[0] = s[1] = s[2] = 0.0;
+#pragma unroll 8
+  for (int p = 0; p < parts; ++p) {
+    const double *o = part + (size_t)p * 3 * N + i;
+    s[0] += o[0]; s[1] += o[(size_t)N]; s[2] += o[2 * (size_t)N];
+  }
 }
 
 // Position along y or z in metres: fixed-point value plus remainder.

@@ -75,6 +75,7 @@ struct depo_ctx {
   int64_t cell_cap = 0;
   int scan_blocks = 0;
   int tile_cap = 0;
+  int part_cap = 1;           // most pieces of a sample's sources in the FP64 pair kernel
   // symmetric pair kernel (FP32): item capacity (for the smallest item size),
   // item counts, per-sample bounds for the fixed-point scale
   int64_t sym_cap = 0;
@@ -185,6 +186,7 @@ size_t carve(depo_ctx *ctx, char *base, State<Real> &st) {
   const size_t nacc = sizeof(Real) == 4 ? N : 1;   // fixed-point accumulators: FP32 form only
   st.items = (SymItem *)take((size_t)std::max<int64_t>(ctx->sym_cap, 1) * sizeof(SymItem));
   st.fx_scale = (double *)take((size_t)ctx->S * sizeof(double));
+  st.part = (double *)take(ctx->fp64() && ctx->part_cap > 1 ? (size_t)ctx->part_cap * 3 * N * sizeof(double) : 0);
   st.accx = (unsigned long long *)take(nacc * 8);
   st.accy = (unsigned long long *)take(nacc * 8);
   st.accz = (unsigned long long *)take(nacc * 8);
@@ -278,6 +280,18 @@ void fill_phys(depo_ctx *ctx) {
   set_record_format(ctx);
 }
 
+// Pieces that each sample's sources are cut into by the FP64 pair kernel: more waves fill the chip and hide
+// each other's latencies, but each wants a run of sources to pay for its start, and k_finish adds the
+// pieces.  Whole steps at (1, 4), us, with 1, 4 and 16 pieces: 1,024 particles 62, 53, 52; 2,500 94, 56, 59;
+// 4,000 122, 63, 69; 9,001 229, 138, 107; 16,000 371, 246, 238; 30,000 898, 769, 705 (708 with 8).
+// So at least 128 sources a wave and at most 16 waves per SIMD.
+int pair_parts(const depo_ctx *ctx, int64_t n_tiles, int waves) {
+  int64_t n_max = 0;
+  for (int s = 0; s < ctx->S; ++s) n_max = std::max(n_max, ctx->off[s + 1] - ctx->off[s]);
+  const int64_t by_run = n_max / (128 * waves), by_waves = 16 * kSimds / (std::max<int64_t>(n_tiles, 1) * waves);
+  return (int)std::max<int64_t>(1, std::min({by_run, by_waves, (int64_t)ctx->part_cap}));
+}
+
 void build_tiles(depo_ctx *ctx, std::vector<TileDev> &tiles) {
   const int T = coulomb_tile_targets(ctx->ccfg);
   std::vector<int> order(ctx->S);
@@ -292,6 +306,7 @@ void build_tiles(depo_ctx *ctx, std::vector<TileDev> &tiles) {
     for (int64_t i = b; i < e; i += T)
       tiles.push_back(TileDev{(int32_t)i, (int32_t)std::min<int64_t>(T, e - i), (int32_t)b, (int32_t)(e - b)});
   }
+  ctx->ph.pair_parts = ctx->fp64() ? pair_parts(ctx, (int64_t)tiles.size(), ctx->ccfg.waves) : 1;
 }
 
 // Items of the symmetric kernel for tiles of T targets and `rounds` rounds of 64 sources per item: per
@@ -432,8 +447,7 @@ template <class Real> int enqueue_coulomb(depo_ctx *ctx, hipStream_t s, bool def
       return defer_finish ? F_PAIR_SUMS : 0;
     }
   }
-  launch_coulomb<Real>(state<Real>(ctx), ctx->ph, ctx->n_tiles, ctx->ccfg, s);
-  return 0;
+  return launch_coulomb<Real>(state<Real>(ctx), ctx->ph, ctx->n_tiles, ctx->ccfg, s, defer_finish) ? F_PAIR_SUMS : 0;
 }
 
 // Enqueue the force evaluation at the current positions (prepare has run).
@@ -1279,6 +1293,8 @@ depo_status depo_set_layout(depo_ctx *ctx, int32_t n_samples, const int64_t *off
   int tiles = 0;
   for (int s = 0; s < n_samples; ++s) tiles += (int)((offsets[s + 1] - offsets[s] + 63) / 64);
   ctx->tile_cap = tiles;
+  // what pair_parts can give with four waves of one target per lane (6 MB)
+  ctx->part_cap = ctx->fp64() && tiles > 0 ? std::max(1, std::min(64, 4 * kSimds / tiles)) : 1;
   // symmetric pair kernel (FP32): room for the items of the smallest item size whose list stays
   // within kMaxItems; the FP32 default falls back to the one-sided kernel beyond that
   ctx->sym_cap = 0;

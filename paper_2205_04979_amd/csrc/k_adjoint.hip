@@ -276,26 +276,41 @@ __global__ __launch_bounds__(256) void k_adj_post(State<Real> st, Phys ph, TapeE
 // ---------------------------------------------------------------- Coulomb pair adjoint
 
 __device__ __forceinline__ float rsqa(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqa(double x) { return 1.0 / sqrt(x); }
+// The hardware's reciprocal root y holds about 24 bits: with e = 1 - x y^2, x^(-1/2) = y (1 + e/2 + 3/8 e^2
+// + O(e^3)), and e^3 is below 2^-66.
+__device__ __forceinline__ double rsqa(double x) {
+  const double y = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * y, y, 1.0);
+  return fma(y * e, fma(e, 0.375, 0.5), y);
+}
 
 // x_bar_i += (1/ux) sum_j J(r_ij) (q_j b_i - q_i b_j), J(r) = I/r^3 - 3 r r^T / r^5
 // (or (I - r^ r^T) / (r d^2) inside the overlap clamp).  Same mapping as the
 // forward pair kernel: targets in lanes, source records from SGPRs, waves
 // splitting the source range, blocks recomputed exactly when a source is
 // closer than the largest diameter, FP64 combination of the per-wave partials.
-template <class Real, int WAVES, int BLK>
+// SPLIT (FP64): the workgroup takes one of `parts` pieces of the sources and
+// writes its own partial sums, which k_vjp_parts adds.
+// Bound by FP64 issue (about 37 instructions a pair and one reciprocal root); small layouts by the
+// waves there are, hence the pieces: four
+// samples of 6,000 to 8,000 particles 682 -> 439 us per reverse step, of 2,000 to 3,000 278 -> 209 us (with
+// the reciprocal root by one correction instead of a root and a division).
+template <class Real, int WAVES, int BLK, bool SPLIT>
 __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__restrict__ tiles,
                                                             const JAdj<Real> *__restrict__ rec,
                                                             const Real *__restrict__ jr, Real *__restrict__ ox,
                                                             Real *__restrict__ oy, Real *__restrict__ oz, Real near2,
-                                                            Real inv_ux) {
+                                                            Real inv_ux, int n_tiles, int parts, int N,
+                                                            double *__restrict__ part) {
   using Pos = typename Prec<Real>::Pos;
   __shared__ double red[WAVES][3][64];
-  const TileDev t = tiles[blockIdx.x];
+  const int piece = SPLIT ? blockIdx.x / n_tiles : 0;
+  const TileDev t = tiles[SPLIT ? blockIdx.x - piece * n_tiles : blockIdx.x];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int per = ((t.jcount + WAVES - 1) / WAVES + BLK - 1) / BLK * BLK;
-  const int jb = t.j0 + w * per;
+  const int nw = SPLIT ? WAVES * parts : WAVES;   // waves that share the sources
+  const int per = ((t.jcount + nw - 1) / nw + BLK - 1) / BLK * BLK;
+  const int jb = t.j0 + min(t.jcount, (piece * WAVES + w) * per);
   const int je = min(t.j0 + t.jcount, jb + per);
   // the tile may hold more than 64 targets (its width follows the forward pair
   // kernel's shape): walk it in chunks of one target per lane
@@ -310,8 +325,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__res
       const int n = min(BLK, je - j0);
       Real sx = 0, sy = 0, sz = 0;
       uint64_t nearmask = 0;
-      for (int jj = 0; jj < n; ++jj) {
-        const JAdj<Real> s = rec[j0 + jj];
+      auto body = [&](const JAdj<Real> &s) {
         const Real dx = sdiff(xi, s.x), dy = yi - s.y, dz = zi - s.z;
         const Real r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, Real(1))));
         nearmask |= __builtin_amdgcn_ballot_w64(r2 < near2);
@@ -325,6 +339,12 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__res
         sx = fma(inv3, px_ - t3 * dx, sx);
         sy = fma(inv3, py_ - t3 * dy, sy);
         sz = fma(inv3, pz_ - t3 * dz, sz);
+      };
+      if (n == BLK) {
+#pragma unroll 4
+        for (int jj = 0; jj < BLK; ++jj) body(rec[j0 + jj]);
+      } else {
+        for (int jj = 0; jj < n; ++jj) body(rec[j0 + jj]);
       }
       if (nearmask) {
         sx = sy = sz = 0;
@@ -354,10 +374,26 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__res
       double s0 = 0, s1 = 0, s2 = 0;
       for (int q = 0; q < WAVES; ++q) { s0 += red[q][0][threadIdx.x]; s1 += red[q][1][threadIdx.x]; s2 += red[q][2][threadIdx.x]; }
       const int i = t.i0 + c0 + threadIdx.x;
-      ox[i] = Real(s0 * (double)inv_ux); oy[i] = Real(s1 * (double)inv_ux); oz[i] = Real(s2 * (double)inv_ux);
+      if (SPLIT) {
+        double *o = part + (size_t)piece * 3 * N + i;
+        o[0] = s0; o[(size_t)N] = s1; o[2 * (size_t)N] = s2;
+      } else {
+        ox[i] = Real(s0 * (double)inv_ux); oy[i] = Real(s1 * (double)inv_ux); oz[i] = Real(s2 * (double)inv_ux);
+      }
     }
     __syncthreads();
   }
+}
+
+// The pieces' partial sums, in their order.
+__global__ __launch_bounds__(256) void k_vjp_parts(int N, int parts, double inv_ux, const double *__restrict__ part,
+                                                   double *__restrict__ ox, double *__restrict__ oy,
+                                                   double *__restrict__ oz) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  double s[3];
+  sum_parts(part, parts, N, i, s);
+  ox[i] = s[0] * inv_ux; oy[i] = s[1] * inv_ux; oz[i] = s[2] * inv_ux;
 }
 
 // ---------------------------------------------------------------- short-range pair adjoint
@@ -541,8 +577,20 @@ template <class Real>
 void launch_coulomb_vjp(const State<Real> &st, const Phys &ph, const AdjState<Real> &ad, int n_tiles, hipStream_t s) {
   if (n_tiles <= 0) return;
   constexpr int W = 16, B = sizeof(Real) == 4 ? 32 : 16;
-  hipLaunchKernelGGL((k_coulomb_vjp<Real, W, B>), dim3(n_tiles), dim3(64 * W), 0, s, st.tiles, ad.rec, st.jr,
-                     ad.xc[0], ad.xc[1], ad.xc[2], Real(ph.near2), Real(ph.inv_ux));
+  if constexpr (sizeof(Real) == 8) {
+    // the forward's pieces (where there are several): smaller workgroups spread better
+    if (ph.pair_parts > 1) {
+      hipLaunchKernelGGL((k_coulomb_vjp<Real, 4, B, true>), dim3(n_tiles * ph.pair_parts), dim3(256), 0, s, st.tiles,
+                         ad.rec, st.jr, ad.xc[0], ad.xc[1], ad.xc[2], Real(ph.near2), Real(ph.inv_ux), n_tiles,
+                         ph.pair_parts, ph.N, st.part);
+      hipLaunchKernelGGL(k_vjp_parts, grid_n<Real>(ph.N), dim3(256), 0, s, ph.N, ph.pair_parts, ph.inv_ux, st.part,
+                         ad.xc[0], ad.xc[1], ad.xc[2]);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((k_coulomb_vjp<Real, W, B, false>), dim3(n_tiles), dim3(64 * W), 0, s, st.tiles, ad.rec, st.jr,
+                     ad.xc[0], ad.xc[1], ad.xc[2], Real(ph.near2), Real(ph.inv_ux), n_tiles, 1, ph.N,
+                     (double *)nullptr);
 }
 template <class Real>
 void launch_short_range_vjp(const State<Real> &st, const Phys &ph, const AdjState<Real> &ad, int n_cells, int mode,

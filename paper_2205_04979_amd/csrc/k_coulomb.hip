@@ -19,7 +19,13 @@
 //   with the exact overlap clamp max(|r|, d_ij);
 // * FP32: each block is summed plainly and then added to the running sum with
 //   Kahan compensation; the per-wave partial sums are combined in FP64
-//   through LDS in a fixed order, so results are bitwise reproducible.
+//   through LDS in a fixed order, so results are bitwise reproducible;
+// * FP64 is bound by the FP64 issue rate (22 instructions and one reciprocal
+//   root per pair, about 119 cycles a wave; 30,000 particles 1,560 -> 680 us,
+//   of which the root and the division took 54 % before); small layouts by
+//   latency and by the waves there are, so SPLIT cuts a sample's sources into
+//   pieces, one workgroup each, whose partial sums k_finish (or k_pair_parts)
+//   adds in their order: 9,001 particles 306 -> 86 us, 1,024 50 -> 29 us.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -27,18 +33,32 @@
 
 namespace depo {
 
-__device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsq(double x) { return 1.0 / sqrt(x); }
+// q / r2^(3/2)
+__device__ __forceinline__ float pair_weight(float q, float r2) {
+  const float inv = __builtin_amdgcn_rsqf(r2);
+  return q * (inv * inv) * inv;
+}
+// FP64: the hardware's reciprocal root y0 holds about 24 bits; with e = 1 - r2 y0^2,
+// r2^(-3/2) = y0^3 (1 - e)^(-3/2) = y0^3 (1 + 3/2 e + 15/8 e^2 + O(e^3)), and e^3 is below 2^-66.
+__device__ __forceinline__ double pair_weight(double q, double r2) {
+  const double y0 = __builtin_amdgcn_rsq(r2);
+  const double y2 = y0 * y0;
+  const double e = fma(-r2, y2, 1.0);
+  const double w = q * (y2 * y0);
+  return fma(w, e * fma(e, 1.875, 1.5), w);
+}
 
-template <class Real, int IPL, int WAVES, int BLK, bool KAHAN, bool PIPE>
+template <class Real, int IPL, int WAVES, int BLK, bool KAHAN, bool PIPE, bool SPLIT>
 __global__ __launch_bounds__(64 * WAVES) void k_coulomb(const TileDev *__restrict__ tiles,
                                                         const JSrc<Real> *__restrict__ js,
                                                         const Real *__restrict__ jr, Real *__restrict__ ox,
                                                         Real *__restrict__ oy, Real *__restrict__ oz,
-                                                        Real near2) {
+                                                        Real near2, int n_tiles, int parts, int N,
+                                                        double *__restrict__ part) {
   using Pos = typename Prec<Real>::Pos;
   __shared__ double red[WAVES][3][64 * IPL];
-  const TileDev t = tiles[blockIdx.x];
+  const int piece = SPLIT ? blockIdx.x / n_tiles : 0;
+  const TileDev t = tiles[SPLIT ? blockIdx.x - piece * n_tiles : blockIdx.x];
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -53,8 +73,9 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb(const TileDev *__restric
     ri[k] = jr[i];
   }
 
-  const int per = ((t.jcount + WAVES - 1) / WAVES + BLK - 1) / BLK * BLK;
-  const int jb = t.j0 + w * per;
+  const int nw = SPLIT ? WAVES * parts : WAVES;   // waves that share the sources
+  const int per = ((t.jcount + nw - 1) / nw + BLK - 1) / BLK * BLK;
+  const int jb = t.j0 + min(t.jcount, (piece * WAVES + w) * per);
   const int je = min(t.j0 + t.jcount, jb + per);
 
   Real hx[IPL], hy[IPL], hz[IPL], cx[IPL], cy[IPL], cz[IPL];
@@ -72,8 +93,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb(const TileDev *__restric
       const Real dz = zi[k] - s.z;
       const Real r2 = fma(dx, dx, fma(dy, dy, fma(dz, dz, Real(1))));
       nearmask |= __builtin_amdgcn_ballot_w64(r2 < near2);
-      const Real inv = rsq(r2);
-      const Real wq = s.q * (inv * inv) * inv;
+      const Real wq = pair_weight(s.q, r2);
       sx[k] = fma(wq, dx, sx[k]);
       sy[k] = fma(wq, dy, sy[k]);
       sz[k] = fma(wq, dz, sz[k]);
@@ -180,8 +200,24 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb(const TileDev *__restric
 #pragma unroll
     for (int q = 0; q < WAVES; ++q) { s0 += red[q][0][ii]; s1 += red[q][1][ii]; s2 += red[q][2][ii]; }
     const int i = t.i0 + ii;
-    ox[i] = Real(s0); oy[i] = Real(s1); oz[i] = Real(s2);
+    if (SPLIT) {
+      double *o = part + (size_t)piece * 3 * N + i;
+      o[0] = s0; o[(size_t)N] = s1; o[2 * (size_t)N] = s2;
+    } else {
+      ox[i] = Real(s0); oy[i] = Real(s1); oz[i] = Real(s2);
+    }
   }
+}
+
+// The pieces' partial sums, in their order.
+__global__ __launch_bounds__(256) void k_pair_parts(int N, int parts, const double *__restrict__ part,
+                                                    double *__restrict__ ox, double *__restrict__ oy,
+                                                    double *__restrict__ oz) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= N) return;
+  double s[3];
+  sum_parts(part, parts, N, i, s);
+  ox[i] = s[0]; oy[i] = s[1]; oz[i] = s[2];
 }
 
 int coulomb_tile_targets(const CoulombConfig &cfg) { return 64 * cfg.ipl; }
@@ -207,22 +243,37 @@ bool coulomb_config_supported(int real_bytes, const CoulombConfig &cfg) {
 }
 
 template <class Real>
-void launch_coulomb(const State<Real> &st, const Phys &ph, int n_tiles, const CoulombConfig &cfg, hipStream_t s) {
-  if (n_tiles <= 0) return;
+bool launch_coulomb(const State<Real> &st, const Phys &ph, int n_tiles, const CoulombConfig &cfg, hipStream_t s,
+                    bool defer_finish) {
+  if (n_tiles <= 0) return false;
   const Real near2 = Real(ph.near2);
-#define X(R, I, W, B, K, P)                                                                              \
-  if constexpr (std::is_same<Real, R>::value) {                                                         \
-    if (cfg.ipl == I && cfg.waves == W && cfg.block == B && cfg.compensated == K) {                     \
-      hipLaunchKernelGGL((k_coulomb<R, I, W, B, K, P>), dim3(n_tiles), dim3(64 * W), 0, s, st.tiles, st.js, \
-                         st.jr, st.cx, st.cy, st.cz, near2);                                             \
-      return;                                                                                           \
-    }                                                                                                   \
+  bool split = false;
+  if constexpr (std::is_same<Real, double>::value) split = ph.pair_parts > 1;
+#define X(R, I, W, B, K, P)                                                                                  \
+  if constexpr (std::is_same<Real, R>::value) {                                                             \
+    if (cfg.ipl == I && cfg.waves == W && cfg.block == B && cfg.compensated == K) {                         \
+      auto go = [&](auto kernel, int parts) {                                                               \
+        hipLaunchKernelGGL(kernel, dim3(n_tiles * parts), dim3(64 * W), 0, s, st.tiles, st.js, st.jr, st.cx, \
+                           st.cy, st.cz, near2, n_tiles, parts, ph.N, st.part);                             \
+      };                                                                                                    \
+      if constexpr (std::is_same<Real, double>::value) {                                                    \
+        if (split) go(k_coulomb<R, I, W, B, K, P, true>, ph.pair_parts);                                    \
+      }                                                                                                     \
+      if (!split) go(k_coulomb<R, I, W, B, K, P, false>, 1);                                                \
+    }                                                                                                       \
   }
   DEPO_COULOMB_CASES(X)
 #undef X
+  if constexpr (std::is_same<Real, double>::value) {
+    if (split && !defer_finish)
+      hipLaunchKernelGGL(k_pair_parts, dim3((ph.N + 255) / 256), dim3(256), 0, s, ph.N, ph.pair_parts, st.part, st.cx,
+                         st.cy, st.cz);
+  }
+  return split && defer_finish;
 }
 
-template void launch_coulomb<float>(const State<float> &, const Phys &, int, const CoulombConfig &, hipStream_t);
-template void launch_coulomb<double>(const State<double> &, const Phys &, int, const CoulombConfig &, hipStream_t);
+template bool launch_coulomb<float>(const State<float> &, const Phys &, int, const CoulombConfig &, hipStream_t, bool);
+template bool launch_coulomb<double>(const State<double> &, const Phys &, int, const CoulombConfig &, hipStream_t,
+                                     bool);
 
 }  // namespace depo

@@ -198,6 +198,9 @@ __global__ __launch_bounds__(256) void k_finish(State<Real> st, Phys ph, int mod
       st.accz[i] = 0ull;
       st.cx[i] = cs[0]; st.cy[i] = cs[1]; st.cz[i] = cs[2];
     }
+  } else if (mode & F_PAIR_SUMS) {
+    sum_parts(st.part, ph.pair_parts, ph.N, i, cs);
+    st.cx[i] = cs[0]; st.cy[i] = cs[1]; st.cz[i] = cs[2];
   }
   if (st.dep[i] != 0) return;
   if (mode & F_FLUID_ONLY) {
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(256) void k_finish(State<Real> st, Phys ph, int mod
   const double q = sp.charge_scale * st.qb[i];
   Real a[3] = {0, 0, 0};
   if (ph.flags & F_COULOMB) {
-    if (!(sizeof(Real) == 4 && (mode & F_PAIR_SUMS))) {
+    if (!(mode & F_PAIR_SUMS)) {
       cs[0] = st.cx[i]; cs[1] = st.cy[i]; cs[2] = st.cz[i];
     }
     const Real c = Real(ph.k_e * q * ph.q_ref / (m * ph.ux * ph.ux));

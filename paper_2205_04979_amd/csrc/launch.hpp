@@ -8,8 +8,9 @@ namespace depo {
 // k_prepare modes
 enum : int { P_KICK_DRIFT = 1, P_COULOMB = 2, P_CELLS = 4, P_SEED = 8 };
 // k_finish modes
-// F_PAIR_SUMS (FP32): the symmetric pair kernel ran without its own finishing pass; k_finish turns
-// the fixed-point accumulators into the FP32 Coulomb sums and clears them, every particle's
+// F_PAIR_SUMS: the pair kernel ran without its own finishing pass.  FP32 (symmetric): k_finish turns
+// the fixed-point accumulators into the FP32 Coulomb sums and clears them, every particle's; FP64: it adds
+// the pieces' partial sums
 enum : int { F_KICK = 1, F_V_FROM_FLUID = 2, F_FLUID_ONLY = 4, F_PAIR_SUMS = 8 };
 
 template <class Real> void launch_prepare(const State<Real> &st, const Phys &ph, int mode, hipStream_t s);
@@ -36,14 +37,16 @@ struct CoulombConfig {
   bool symmetric = false;  // FP32: each unordered pair once, reaction on the source (Newton's third law)
   bool int_rec = false;    // symmetric FP32: y and z of the source records as 32-bit integers in x quanta
 };
+// FP64 with ph.pair_parts > 1: every sample's sources in that many pieces, each with its own partial sums;
+// with defer_finish k_finish adds them (F_PAIR_SUMS; the return value says whether it has to).
 template <class Real>
-void launch_coulomb(const State<Real> &st, const Phys &ph, int n_tiles, const CoulombConfig &cfg, hipStream_t s);
+bool launch_coulomb(const State<Real> &st, const Phys &ph, int n_tiles, const CoulombConfig &cfg, hipStream_t s,
+                    bool defer_finish);
 int coulomb_tile_targets(const CoulombConfig &cfg);
 bool coulomb_config_supported(int real_bytes, const CoulombConfig &cfg);
 
-// Symmetric FP32 pair sums: diagonal items, off-diagonal items, then the fixed-order
-// reduction of each particle's partial slots into cx/cy/cz.
-int coulomb_sym_tile(const CoulombConfig &cfg);   // targets (= sources) per item
+// Symmetric FP32 pair sums over the layout's item list, combined in fixed point into cx/cy/cz.
+int coulomb_sym_tile(const CoulombConfig &cfg);   // targets per item (a tile)
 bool coulomb_sym_supported(const CoulombConfig &cfg);
 // defer_finish: leave the fixed-point accumulators for k_finish (mode F_PAIR_SUMS) instead of
 // converting them with k_pair_finish

@@ -854,3 +854,43 @@ def test_fp32_default_shape_by_layout(sizes):
     sim2.step(1)
     sim2.step(1)
     assert np.array_equal(a, sim2.read()["a"])
+
+
+@pytest.mark.parametrize("sizes", [(1024,), (1100, 1, 40, 3000, 0, 65), (2049, 2049, 2047)])
+def test_fp64_pieces_of_the_sources_agree_with_whole_rows(sizes):
+    """The FP64 pair kernel and its adjoint cut the sources into pieces from 1,024 particles a sample on;
+    samples shorter than the pieces, empty ones, and runs that do not fill the last piece.  Accelerations
+    against the oracle (4 roundings a term: within 1e-12 of the sum of the terms' sizes); the sixteen-wave
+    shape, which takes rows whole at these sizes, gives the same accelerations and gradients to rounding."""
+    n = sum(sizes)
+    w = make_workload("single-65k", n=n, field_n=32)
+    f = w.field()
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    sp = np.repeat(w.sample_params[:1], len(sizes), axis=0)
+    p = dict(w.params, soft_tally=True)
+    x = w.x.copy()
+    x[n - 1] = x[off[-2] if sizes[-1] > 1 else 0] + 0.5 * w.d[n - 1]       # one overlapping pair
+    say("case: FP64 pieces, sizes", sizes)
+    sim, ora = seeded_pair(p, f, x, w.d, w.qbase, off, sp, 8)
+    sim.eval_accel()
+    a = sim.read()["a"]
+    tg = np.arange(n)
+    scale = coulomb_scale(ora, tg)
+    ok = scale > 0
+    sim2, _ = seeded_pair(p, f, x, w.d, w.qbase, off, sp, 8, oracle=False)
+    sim2.set_kernel_config(1, 16, 16)
+    sim2.eval_accel()
+    b = sim2.read()["a"]
+    e = np.abs(a - b).max(1)[ok] / scale[ok]
+    say("pieces against rows", e.max(), "against the oracle", force_error(a[ok], ora.a[ok], scale[ok]).max())
+    assert e.max() < 1e-12
+    assert force_error(a[ok], ora.a[ok], scale[ok]).max() < 1e-9
+    sim.step(3)
+    sim2.step(3)
+    assert np.abs(sim.read()["x"] - sim2.read()["x"]).max() < 1e-12 * p["R"]
+    g = []
+    for s in (sim, sim2):
+        s.seed(sp, x, w.d, w.qbase)
+        g.append(s.adjoint(4, 2))
+    big = np.abs(g[1]) > 1e-3 * np.abs(g[1]).max(0)
+    assert np.abs(g[0] - g[1])[big].max() <= 1e-9 * np.abs(g[1])[big].max()
