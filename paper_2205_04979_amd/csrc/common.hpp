@@ -77,6 +77,7 @@ struct Phys {
   double g_body[3];
   double E_young, delta_c, acont_coef;
   double soft_eps, soft_rate;     // eps_s = soft_eps d ; dl/dt = sigma(-g/eps_s) * soft_rate
+  int32_t cells_fused;            // the cell list is built by one kernel, without the histogram of k_prepare
   int32_t pair_parts;             // pieces of each sample's sources in the FP64 pair kernel
   double near2;                   // (largest diameter / ux)^2: pair-kernel exact-path threshold
 };
@@ -254,6 +255,49 @@ __device__ __forceinline__ double pair_gap(Pos xi, Pos yi, Pos zi, Pos xj, Pos y
   dist = sqrt(r2);
   return (r2 - s * s) / (dist + s);
 }
+
+// The gap of pair_gap where it is at most `most`; where it surely is more (the squared distance says so
+// with a margin far above rounding), any larger value, without the root and the division.
+template <class Pos>
+__device__ __forceinline__ double pair_gap_within(double most, Pos xi, Pos yi, Pos zi, Pos xj, Pos yj, Pos zj,
+                                                  double drx, double dry, double drz, double ux, double ur, double s,
+                                                  double &dx, double &dy, double &dz, double &dist) {
+  dx = ((double)as_signed(Pos(xi - xj)) + drx) * ux;
+  dy = ((double)as_signed(Pos(yi - yj)) + dry) * ur;
+  dz = ((double)as_signed(Pos(zi - zj)) + drz) * ur;
+  const double r2 = dx * dx + dy * dy + dz * dz;
+  const double far = s + most;
+  if (r2 > far * far * (1.0 + 1e-9)) { dist = far; return __builtin_inf(); }
+  dist = sqrt(r2);
+  return (r2 - s * s) / (dist + s);
+}
+
+// Lanes per particle of the short-range walks, its rows of cells dealt out among them.  A walk is a chain of
+// dependent reads, so small launches last as long as their longest one: 3,001 particles 10.5 -> 7.7 us with
+// two lanes, 7.2 with four; 2^20 in cell order loses 1 % of a step with four, nothing with two.
+constexpr int kShortRangeLanes = 2;
+
+// Rows of neighbour cells (contiguous along z, so one run of the cell-ordered index) that a particle's
+// short-range walk visits: x outer, y inner, in the order of the cells.
+struct NearRows {
+  int cx, cy, x0, y0, ny, n, z0, z1;
+  __device__ __forceinline__ NearRows(int cx_, int cy_, int cz, int mx, int my, int mz, const SampleDev &sp) {
+    cx = cx_; cy = cy_;
+    x0 = -(mx & 1);
+    y0 = (my & 1) && cy > 0 ? -1 : 0;
+    ny = 1 - y0 + ((my & 2) && cy + 1 < sp.ncy ? 1 : 0);
+    n = (1 + (mx & 1) + (mx >> 1)) * ny;
+    z0 = (mz & 1) && cz > 0 ? cz - 1 : cz;
+    z1 = (mz & 2) && cz + 1 < sp.ncz ? cz + 1 : cz;
+  }
+  // first cell of row r, r < n
+  __device__ __forceinline__ int first(int r, const SampleDev &sp) const {
+    const int rx = (r >= ny ? 1 : 0) + (r >= 2 * ny ? 1 : 0);
+    int xx = cx + x0 + rx;
+    xx = xx < 0 ? xx + sp.ncx : (xx >= sp.ncx ? xx - sp.ncx : xx);
+    return sp.cell_base + (xx * sp.ncy + cy + y0 + r - rx * ny) * sp.ncz + z0;
+  }
+};
 
 // Partial pair sums [parts][3][N] of particle i added in the order of the parts.
 __device__ __forceinline__ void sum_parts(const double *__restrict__ part, int parts, int N, int i, double (&s)[3]) {

@@ -281,15 +281,16 @@ void fill_phys(depo_ctx *ctx) {
 }
 
 // Pieces that each sample's sources are cut into by the FP64 pair kernel: more waves fill the chip and hide
-// each other's latencies, but each wants a run of sources to pay for its start, and k_finish adds the
-// pieces.  Whole steps at (1, 4), us, with 1, 4 and 16 pieces: 1,024 particles 62, 53, 52; 2,500 94, 56, 59;
-// 4,000 122, 63, 69; 9,001 229, 138, 107; 16,000 371, 246, 238; 30,000 898, 769, 705 (708 with 8).
-// So at least 128 sources a wave and at most 16 waves per SIMD.
-int pair_parts(const depo_ctx *ctx, int64_t n_tiles, int waves) {
+// each other's latencies, but k_finish adds the pieces.  Pair sums at (1, 4), us, with 1, 4, 16, 32 and 64
+// pieces: 300 particles 21, 16, 12, 14, 17; 1,024 38, 24, 13, 15, 19; 2,500 70, 33, 25, 23, 24; 4,000
+// 99, 41, 33, 30, 42; 9,001 203, 116, 86, 84, 92; 16,000 346, 222, 214, 224, 226; 30,000 872, 745, 680 (682
+// with 8), 682, 682.  So a block of sources a wave, at most 16 waves per SIMD and 32 pieces.
+int pair_parts(const depo_ctx *ctx, int64_t n_tiles, const CoulombConfig &c) {
   int64_t n_max = 0;
   for (int s = 0; s < ctx->S; ++s) n_max = std::max(n_max, ctx->off[s + 1] - ctx->off[s]);
-  const int64_t by_run = n_max / (128 * waves), by_waves = 16 * kSimds / (std::max<int64_t>(n_tiles, 1) * waves);
-  return (int)std::max<int64_t>(1, std::min({by_run, by_waves, (int64_t)ctx->part_cap}));
+  const int64_t run = (int64_t)c.block * c.waves;
+  const int64_t by_waves = 16 * kSimds / (std::max<int64_t>(n_tiles, 1) * c.waves);
+  return (int)std::max<int64_t>(1, std::min({(n_max + run - 1) / run, by_waves, (int64_t)ctx->part_cap}));
 }
 
 void build_tiles(depo_ctx *ctx, std::vector<TileDev> &tiles) {
@@ -306,7 +307,7 @@ void build_tiles(depo_ctx *ctx, std::vector<TileDev> &tiles) {
     for (int64_t i = b; i < e; i += T)
       tiles.push_back(TileDev{(int32_t)i, (int32_t)std::min<int64_t>(T, e - i), (int32_t)b, (int32_t)(e - b)});
   }
-  ctx->ph.pair_parts = ctx->fp64() ? pair_parts(ctx, (int64_t)tiles.size(), ctx->ccfg.waves) : 1;
+  ctx->ph.pair_parts = ctx->fp64() ? pair_parts(ctx, (int64_t)tiles.size(), ctx->ccfg) : 1;
 }
 
 // Items of the symmetric kernel for tiles of T targets and `rounds` rounds of 64 sources per item: per
@@ -633,6 +634,10 @@ depo_status build_samples(depo_ctx *ctx, const depo_sample_params *sp, const dou
   }
   if (cells > ctx->cell_cap) return ctx->fail(DEPO_E_CAPACITY, "cell grid exceeds reserved capacity");
   ctx->n_cells = (int)cells;
+  // One kernel for the cell list where its workgroups, which each read every particle's cell, cost less than the
+  // launches of the general build: 3,001 particles 7.8 us against 18.7; 65,536 18.2 and 22.8; 200,000 34.8
+  // and 29.8, where the histogram that k_prepare then saves still makes up for it; 2^20 310 and 78.
+  ctx->ph.cells_fused = ctx->N <= (1 << 17) ? 1 : 0;
   ctx->dmax_all = dmax_all;
   const double dq = dmax_all * ctx->ph.inv_ux;
   ctx->ph.near2 = dq * dq;
@@ -1293,8 +1298,8 @@ depo_status depo_set_layout(depo_ctx *ctx, int32_t n_samples, const int64_t *off
   int tiles = 0;
   for (int s = 0; s < n_samples; ++s) tiles += (int)((offsets[s + 1] - offsets[s] + 63) / 64);
   ctx->tile_cap = tiles;
-  // what pair_parts can give with four waves of one target per lane (6 MB)
-  ctx->part_cap = ctx->fp64() && tiles > 0 ? std::max(1, std::min(64, 4 * kSimds / tiles)) : 1;
+  // what pair_parts can give with four waves of one target per lane (at most 6 MB)
+  ctx->part_cap = ctx->fp64() && tiles > 0 ? std::max(1, std::min(32, 4 * kSimds / tiles)) : 1;
   // symmetric pair kernel (FP32): room for the items of the smallest item size whose list stays
   // within kMaxItems; the FP32 default falls back to the one-sided kernel beyond that
   ctx->sym_cap = 0;

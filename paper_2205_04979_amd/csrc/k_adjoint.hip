@@ -416,7 +416,8 @@ __device__ __forceinline__ void vdw_force_and_slope(Real gs_m, Real di_m, Real d
 template <class Real>
 __global__ __launch_bounds__(256) void k_short_range_vjp(State<Real> st, Phys ph, AdjState<Real> ad, int n_cells,
                                                          int mode) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  constexpr int G = kShortRangeLanes;
+  const int t = (int)((blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / G), g = threadIdx.x % G;
   if (t >= st.cell_start[n_cells]) return;
   const int i = st.cell_idx[t];
   const SampleDev sp = st.samples[st.sid[i]];
@@ -435,67 +436,66 @@ __global__ __launch_bounds__(256) void k_short_range_vjp(State<Real> st, Phys ph
   Real xb[3] = {0, 0, 0}, vb[3] = {0, 0, 0};
   double gA = 0.0;
   // only the neighbour cells whose shared face is closer than the reach can hold a partner
-  for (int ox = -1; ox <= 1; ++ox) {
-    if ((ox < 0 && !(mx & 1)) || (ox > 0 && !(mx & 2))) continue;
-    int xx = cx + ox;
-    xx = xx < 0 ? xx + sp.ncx : (xx >= sp.ncx ? xx - sp.ncx : xx);
-    for (int oy = -1; oy <= 1; ++oy) {
-      if ((oy < 0 && !(my & 1)) || (oy > 0 && !(my & 2))) continue;
-      const int yy = cy + oy;
-      if (yy < 0 || yy >= sp.ncy) continue;
-      for (int oz = -1; oz <= 1; ++oz) {
-        if ((oz < 0 && !(mz & 1)) || (oz > 0 && !(mz & 2))) continue;
-        const int zz = cz + oz;
-        if (zz < 0 || zz >= sp.ncz) continue;
-        const int c = sp.cell_base + (xx * sp.ncy + yy) * sp.ncz + zz;
-        const int e = st.cell_start[c + 1];
-        for (int k = st.cell_start[c]; k < e; ++k) {
-          const int j = st.cell_idx[k];
-          if (j == i) continue;
-          // the forward's pair geometry and range test (FP64 gap)
-          const double dj_d = st.d[j];
-          double gx, gy, gz, gd;
-          const double gap_d = pair_gap(px, py, pz, st.px[j], st.py[j], st.pz[j], rxi - (double)st.rx[j],
-                                        ryi - (double)st.ry[j], rzi - (double)st.rz[j], ph.ux, ph.ur,
-                                        0.5 * (di_d + dj_d), gx, gy, gz, gd);
-          if (gap_d > 0.25 * fmin(di_d, dj_d) || gd == 0.0) continue;
-          const double inv_d = 1.0 / gd;
-          const Real inv = Real(inv_d);
-          const Real n[3] = {Real(gx * inv_d), Real(gy * inv_d), Real(gz * inv_d)};
-          const Real dj = Real(dj_d);
-          const Real gap = Real(gap_d);
-          const Real mj = Real(ph.mass_coef) * dj * dj * dj;
-          // pair force on i along n: Fs = -F_vdw(gs) + [gap<0] m_eff (K overlap - H v_n)
-          Real Fs = 0, Fr = 0, Fv = 0;
-          Real vrel[3] = {0, 0, 0}, vn = 0;
-          if (vdw) {
-            Real F1, dF1;
-            const bool sat = gap <= dsat;
-            vdw_force_and_slope(sat ? dsat : gap, di, dj, Real(1), F1, dF1);
-            Fs -= A * F1;
-            if (!sat) Fr -= A * dF1;
-            gA -= (double)((wi[0] * n[0] + wi[1] * n[1] + wi[2] * n[2]) * F1);
-          }
-          if (col && gap < Real(0)) {
-            const Real meff = mi * mj / (mi + mj);
-            for (int q = 0; q < 3; ++q) vrel[q] = vi[q] - ad.vp[q][j];
-            vn = vrel[0] * n[0] + vrel[1] * n[1] + vrel[2] * n[2];
-            Fs += meff * (Real(ph.col_K) * (-gap) - Real(ph.col_H) * vn);
-            Fr += meff * -Real(ph.col_K);
-            Fv = meff * -Real(ph.col_H);
-          }
-          if (mode & ADJ_SEED) continue;
-          // omega = a_bar_i/m_i - a_bar_j/m_j
-          const Real om[3] = {wi[0] - ad.ab[0][j] / mj, wi[1] - ad.ab[1][j] / mj, wi[2] - ad.ab[2][j] / mj};
-          const Real on = om[0] * n[0] + om[1] * n[1] + om[2] * n[2];
-          for (int q = 0; q < 3; ++q) {
-            xb[q] += Fr * n[q] * on + Fv * on * (vrel[q] - vn * n[q]) * inv + Fs * inv * (om[q] - n[q] * on);
-            vb[q] += Fv * n[q] * on;
-          }
-        }
+  const NearRows rows(cx, cy, cz, mx, my, mz, sp);
+  for (int r = g; r < rows.n; r += G) {
+    const int c = rows.first(r, sp);
+    const int e = st.cell_start[c + 1 + rows.z1 - rows.z0];
+    for (int k = st.cell_start[c]; k < e; ++k) {
+      const int j = st.cell_idx[k];
+      if (j == i) continue;
+      // the forward's pair geometry and range test (FP64 gap)
+      const double dj_d = st.d[j];
+      double gx, gy, gz, gd;
+      const double most = 0.25 * fmin(di_d, dj_d);
+      const double gap_d = pair_gap_within(most, px, py, pz, st.px[j], st.py[j], st.pz[j], rxi - (double)st.rx[j],
+                                           ryi - (double)st.ry[j], rzi - (double)st.rz[j], ph.ux, ph.ur,
+                                           0.5 * (di_d + dj_d), gx, gy, gz, gd);
+      if (gap_d > most || gd == 0.0) continue;
+      const double inv_d = 1.0 / gd;
+      const Real inv = Real(inv_d);
+      const Real n[3] = {Real(gx * inv_d), Real(gy * inv_d), Real(gz * inv_d)};
+      const Real dj = Real(dj_d);
+      const Real gap = Real(gap_d);
+      const Real mj = Real(ph.mass_coef) * dj * dj * dj;
+      // pair force on i along n: Fs = -F_vdw(gs) + [gap<0] m_eff (K overlap - H v_n)
+      Real Fs = 0, Fr = 0, Fv = 0;
+      Real vrel[3] = {0, 0, 0}, vn = 0;
+      if (vdw) {
+        Real F1, dF1;
+        const bool sat = gap <= dsat;
+        vdw_force_and_slope(sat ? dsat : gap, di, dj, Real(1), F1, dF1);
+        Fs -= A * F1;
+        if (!sat) Fr -= A * dF1;
+        gA -= (double)((wi[0] * n[0] + wi[1] * n[1] + wi[2] * n[2]) * F1);
+      }
+      if (col && gap < Real(0)) {
+        const Real meff = mi * mj / (mi + mj);
+        for (int q = 0; q < 3; ++q) vrel[q] = vi[q] - ad.vp[q][j];
+        vn = vrel[0] * n[0] + vrel[1] * n[1] + vrel[2] * n[2];
+        Fs += meff * (Real(ph.col_K) * (-gap) - Real(ph.col_H) * vn);
+        Fr += meff * -Real(ph.col_K);
+        Fv = meff * -Real(ph.col_H);
+      }
+      if (mode & ADJ_SEED) continue;
+      // omega = a_bar_i/m_i - a_bar_j/m_j
+      const Real om[3] = {wi[0] - ad.ab[0][j] / mj, wi[1] - ad.ab[1][j] / mj, wi[2] - ad.ab[2][j] / mj};
+      const Real on = om[0] * n[0] + om[1] * n[1] + om[2] * n[2];
+      for (int q = 0; q < 3; ++q) {
+        xb[q] += Fr * n[q] * on + Fv * on * (vrel[q] - vn * n[q]) * inv + Fs * inv * (om[q] - n[q] * on);
+        vb[q] += Fv * n[q] * on;
       }
     }
   }
+  // the lanes' sums, pairwise
+#pragma unroll
+  for (int m = 1; m < G; m <<= 1) {
+    for (int q = 0; q < 3; ++q) {
+      xb[q] += __shfl_xor(xb[q], m);
+      vb[q] += __shfl_xor(vb[q], m);
+    }
+    gA += __shfl_xor(gA, m);
+  }
+  if (g != 0) return;
   ad.gA[i] += gA;
   ad.xs[0][i] = xb[0]; ad.xs[1][i] = xb[1]; ad.xs[2][i] = xb[2];
   ad.vs[0][i] = vb[0]; ad.vs[1][i] = vb[1]; ad.vs[2][i] = vb[2];
@@ -595,7 +595,8 @@ void launch_coulomb_vjp(const State<Real> &st, const Phys &ph, const AdjState<Re
 template <class Real>
 void launch_short_range_vjp(const State<Real> &st, const Phys &ph, const AdjState<Real> &ad, int n_cells, int mode,
                             hipStream_t s) {
-  hipLaunchKernelGGL(k_short_range_vjp<Real>, grid_n<Real>(ph.N), dim3(256), 0, s, st, ph, ad, n_cells, mode);
+  hipLaunchKernelGGL(k_short_range_vjp<Real>, grid_n<Real>(ph.N * kShortRangeLanes), dim3(256), 0, s, st,
+                     ph, ad, n_cells, mode);
 }
 template <class Real>
 void launch_adj_pre(const State<Real> &st, const Phys &ph, const TapeEntry<Real> &s0, const AdjState<Real> &ad,

@@ -221,9 +221,13 @@ __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *
         }
       }
       if constexpr (REACT) {
+        // as in ring_round4 (18,000 particles, two targets per lane: 93 -> 87 us; raised for the root
+        // too it gains nothing here)
+        __builtin_amdgcn_s_setprio(1);
         rx = dpp<kWaveRol1>(rx);
         ry = dpp<kWaveRol1>(ry);
         rz = dpp<kWaveRol1>(rz);
+        __builtin_amdgcn_s_setprio(0);
       }
     };
     if constexpr (REACT && IPL == 4 && !INTREC) {

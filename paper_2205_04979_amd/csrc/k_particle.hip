@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void k_prepare(State<Real> st, Phys ph, int mo
       const int cy = box_cell(as_signed(py), sp.ncy);
       const int cz = box_cell(as_signed(pz), sp.ncz);
       c = sp.cell_base + (cx * sp.ncy + cy) * sp.ncz + cz;
-      atomicAdd(&st.cell_count[c], 1);
+      if (!ph.cells_fused) atomicAdd(&st.cell_count[c], 1);
     }
     st.cell_of[i] = c;
   }

@@ -858,10 +858,10 @@ def test_fp32_default_shape_by_layout(sizes):
 
 @pytest.mark.parametrize("sizes", [(1024,), (1100, 1, 40, 3000, 0, 65), (2049, 2049, 2047)])
 def test_fp64_pieces_of_the_sources_agree_with_whole_rows(sizes):
-    """The FP64 pair kernel and its adjoint cut the sources into pieces from 1,024 particles a sample on;
-    samples shorter than the pieces, empty ones, and runs that do not fill the last piece.  Accelerations
-    against the oracle (4 roundings a term: within 1e-12 of the sum of the terms' sizes); the sixteen-wave
-    shape, which takes rows whole at these sizes, gives the same accelerations and gradients to rounding."""
+    """The FP64 pair kernel and its adjoint cut the sources into pieces; samples shorter than the pieces, empty
+    ones, and runs that do not fill the last piece.  Accelerations against the oracle, and against the
+    sixteen-wave shape with its quarter of the pieces (4 roundings a term: within 1e-12 of the sum of the
+    terms' sizes), which gives the same gradients to rounding."""
     n = sum(sizes)
     w = make_workload("single-65k", n=n, field_n=32)
     f = w.field()
@@ -894,3 +894,61 @@ def test_fp64_pieces_of_the_sources_agree_with_whole_rows(sizes):
         g.append(s.adjoint(4, 2))
     big = np.abs(g[1]) > 1e-3 * np.abs(g[1]).max(0)
     assert np.abs(g[0] - g[1])[big].max() <= 1e-9 * np.abs(g[1])[big].max()
+
+
+@pytest.mark.parametrize("real_bytes", [4, 8])
+@pytest.mark.parametrize("sizes,crowd", [((1023,), 0), ((1025, 3, 0, 700), 0), ((9000,), 6000), ((131072,), 0),
+                                         ((131073,), 0)])
+def test_cell_list_in_one_kernel(real_bytes, sizes, crowd):
+    """Short-range forces through the cell list built by one kernel (to 131,072 particles) and by the general
+    build beyond: chunks of 1,024 cells with a remainder, several samples, and a crowd of particles in a
+    few cells (more than a workgroup holds in LDS).  Neighbour counts and accelerations against all pairs
+    of a set of targets (contact and cohesion only, FP64 geometry in both forms: 1e-4 in FP32, 1e-9 in
+    FP64 of the largest), with the overlaps kept away from the clamps; a second build gives the same bits."""
+    if real_bytes == 8 and sizes[0] > 100000:
+        pytest.skip("one precision is enough for the largest")
+    n = sum(sizes)
+    w = make_workload("single-65k", n=n, field_n=32)
+    f = w.field()
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    sp = np.repeat(w.sample_params[:1], len(sizes), axis=0)
+    p = dict(w.params, drag=False, coulomb=False, wall_image=False, wall_vdw=False, vdw=False)
+    rng = np.random.default_rng(n + crowd)
+    x = w.x.copy()
+    d = np.full(n, 10e-6)
+    if crowd:
+        # a cubic grid of the crowd, spaced 1.2 d, near the axis: one or two cells of the coarse grid
+        m = int(np.ceil(crowd ** (1 / 3)))
+        g = np.stack(np.meshgrid(*[np.arange(m)] * 3, indexing="ij"), -1).reshape(-1, 3)[:crowd]
+        x[rng.permutation(n)[:crowd]] = (g + 0.5) * 12e-6 + np.array([0.011, 1e-4, 1e-4])
+    k = rng.permutation(n)
+    for b, e in zip(off[:-1], off[1:]):
+        kk = k[(k >= b) & (k < e)][:200]
+        for i, j in zip(kk[0::2], kk[1::2]):     # contacts overlapping by 1 % to 5 %
+            u = rng.normal(size=3)
+            x[j] = x[i] + u / np.linalg.norm(u) * d[i] * rng.uniform(0.95, 0.99)
+    x[:, 0] = np.mod(x[:, 0], p["L"])
+    say("case: one-kernel cell list, sizes", sizes, "crowd", crowd, "fp", 8 * real_bytes)
+    sim, _ = seeded_pair(p, f, x, d, np.zeros(n), off, sp, real_bytes, oracle=False, v0=np.zeros((n, 3)))
+    sim.eval_accel()
+    g0 = sim.read()
+    xs = g0["x"]
+    m = p["rho_p"] * np.pi * d ** 3 / 6
+    tau = p["tau_col_steps"] * p["dt"]
+    K = (np.pi ** 2 + np.log(p["e_pp"]) ** 2) / tau ** 2
+    worst, top = 0.0, 0.0
+    for b, e in zip(off[:-1], off[1:]):
+        for i in np.concatenate([k[(k >= b) & (k < e)][:60], np.arange(b, min(b + 3, e))]):
+            r = xs[i] - xs[b:e]
+            r[:, 0] -= p["L"] * np.round(r[:, 0] / p["L"])
+            dist = np.linalg.norm(r, axis=1)
+            dist[i - b] = np.inf
+            gap = dist - d[i]
+            assert g0["neighbours"][i] == np.count_nonzero(gap <= 0.25 * d[i]), i
+            hit = np.nonzero(gap < 0)[0]
+            a = sum((0.5 * K * -gap[j] * r[j] / dist[j] for j in hit), np.zeros(3))
+            worst, top = max(worst, np.abs(a - g0["a"][i]).max()), max(top, np.abs(a).max())
+    say("largest deviation", worst, "of", top)
+    assert top > 0 and worst <= (1e-4 if real_bytes == 4 else 1e-9) * top
+    sim.eval_accel()
+    assert np.array_equal(g0["a"], sim.read()["a"])
