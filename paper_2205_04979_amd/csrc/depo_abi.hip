@@ -192,17 +192,17 @@ size_t carve(depo_ctx *ctx, char *base, State<Real> &st) {
   st.accz = (unsigned long long *)take(nacc * 8);
   if (ctx->p3m_cfg) {
     P3mDev &m = ctx->pm;
-    const size_t total = (size_t)m.nx * m.P * m.P, ncell = (size_t)m.ncx * m.ncy * m.ncy;
-    const size_t me = sizeof(Real) == 4 ? sizeof(float2) : sizeof(double2);   // mesh element
-    for (int c = 0; c < 3; ++c) m.ghat[c] = take(total * me);
-    m.rho = take(2 * total * me);   // rho, then work
-    m.work = m.rho ? (void *)((char *)m.rho + total * me) : nullptr;
+    const size_t ncell = (size_t)m.ncx * m.ncy * m.ncy;
+    const size_t half = (size_t)p3m_spectrum_values(m) * 2 * sizeof(Real);
+    for (int c = 0; c < 3; ++c) m.ghat[c] = take(half);
+    m.spec = take(p3m_mesh_bytes(m, sizeof(Real)));   // also the scratch mesh of the Green's function set-up
+    m.field = m.spec ? (void *)((char *)m.spec + 3 * half) : nullptr;
+    m.twiddles = take(512 * 2 * sizeof(Real));
     m.qmesh = (unsigned long long *)take((size_t)m.nx * m.nc * m.nc * 8);
     m.slong = (double *)take(3 * N * sizeof(double));
     m.cell_of = (int32_t *)take(N * 4);
     m.counts = (int32_t *)take(ncell * 4);
     m.starts = (int32_t *)take((ncell + 1) * 4);
-    m.fill = (int32_t *)take(ncell * 4);
     m.sorted = (int32_t *)take(N * 4);
     m.rec = take(N * 5 * sizeof(typename Prec<Real>::Pos));
     m.table = (float2 *)take(2049 * sizeof(float2));   // 2,048 intervals + the terminating (0, 0)
@@ -676,7 +676,6 @@ template <class Real> depo_status upload_tables(depo_ctx *ctx, hipStream_t s) {
   if (ctx->p3m_cfg) {
     if (depo_status u = upload_p3m_scale(ctx, s); u != DEPO_OK) return u;
     const P3mDev &m = ctx->pm;
-    launch_clear_int((int32_t *)m.qmesh, 2 * (size_t)m.nx * m.nc * m.nc, s);
     launch_clear_int(m.counts, (size_t)m.ncx * m.ncy * m.ncy, s);
     if (!ctx->p3m_green) {
       p3m_setup_green(m, ctx->p.L, kP3mImages, sizeof(Real) == 4, s);
@@ -1324,6 +1323,7 @@ depo_status depo_set_layout(depo_ctx *ctx, int32_t n_samples, const int64_t *off
     m.nx = ctx->p3m_nx;
     m.nc = ctx->p3m_nc;
     m.P = 2 * m.nc;
+    m.xs = p3m_plane_values(m, ctx->p.real_bytes);
     m.hx = ctx->p.L / m.nx;
     m.hy = 2.0 * ctx->p.R / (m.nc - 3);
     m.alpha = ctx->p3m_alpha_h / std::max(m.hx, m.hy);

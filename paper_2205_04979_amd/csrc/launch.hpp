@@ -60,16 +60,22 @@ struct P3mDev {
   double hx, hy;          // mesh spacings [m]
   double alpha, rmax;     // splitting parameter [1/m] and short-range cutoff [m]
   const double *q_scale;  // device: fixed-point units per unit of scaled charge
-  // mesh arrays of nx x P x P complex values: float2 in the FP32 form, double2 in the FP64 form
+  // complex values: float2 in the FP32 form, double2 in the FP64 form; half spectra (kz < P/2 as
+  // [nx] planes of xs values, [P][P/2] and padding, then the plane kz = P/2 as [nx][P])
+  int64_t xs;
   void *ghat[3];          // transformed, deconvolved Green's function per field component
-  void *rho, *work;       // transformed charge; one field component (FP32 form: adjacent, so that
-                          // together they hold one double2 mesh for the Green's function set-up)
-  unsigned long long *qmesh;   // fixed-point TSC charge, nx x nc x nc (zero between steps)
+  void *spec;             // three spectra (the charge's in the first), p3m_spectrum_values each
+  void *field;            // field components at the nodes, nx x nc x nc x 4 reals, behind spec
+  void *twiddles;         // 512 complex roots of unity
+  unsigned long long *qmesh;   // fixed-point TSC charge, nx x nc x nc
   double *slong;          // [3][N] long-range part at the particles [1/m^2]
-  int32_t *cell_of, *counts, *starts, *fill, *sorted;   // short-range cell list
+  int32_t *cell_of, *counts, *starts, *sorted;   // short-range cell list
   void *rec;              // cell-sorted source records of the short-range pass (N records)
   float2 *table;          // tabulated short-range profile (FP32 form), 2048 intervals + (0, 0)
 };
+int64_t p3m_plane_values(const P3mDev &m, size_t real_bytes);   // xs
+int64_t p3m_spectrum_values(const P3mDev &m);                  // complex values of a half spectrum
+size_t p3m_mesh_bytes(const P3mDev &m, size_t real_bytes);     // spec and field, at least one full FP64 mesh
 void p3m_setup_green(const P3mDev &m, double L, int images, bool fp32_mesh, hipStream_t s);
 template <class Real> void launch_p3m(const State<Real> &st, const Phys &ph, const P3mDev &m, hipStream_t s);
 

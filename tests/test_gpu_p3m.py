@@ -319,3 +319,60 @@ def test_p3m_crowded_cells_against_oracle_p3m(real_bytes):
     else:
         assert np.all(e <= p3m_fp32_bound(w, pooled_nearest(ora, tg)))
     sim.close()
+
+
+@pytest.mark.parametrize("real_bytes", [8, 4])
+@pytest.mark.parametrize("mesh_x,mesh_yz,alpha_h,rmax_alpha", [(16, 16, 1.0, 3.0), (16, 32, 1.0, 3.5), (64, 16, 0.5, 3.5)])
+def test_p3m_small_meshes_and_edges_of_cells(real_bytes, mesh_x, mesh_yz, alpha_h, rmax_alpha):
+    """The smallest meshes (every kind of line length in one workgroup, three short-range cells along x at
+    the longest cutoff), with particles at both ends of the period, near the wall, in one crowd (several
+    batches of sources for its clusters, one cell with most particles) and an overlapping pair: every
+    particle against the P3M oracle at the bounds above."""
+    from tests.oracle_pool import coulomb_magnitude_sum, nearest_distance
+    from oracle.sim import OracleSim
+    w = make_workload("single-65k", n=523, field_n=16, **COULOMB_ONLY)
+    f = w.field()
+    R, L = w.params["R"], w.params["L"]
+    rng = np.random.default_rng(5)
+    w.x[:20, 0] = np.where(np.arange(20) % 2 == 0, 1e-7, L - 1e-7) * (1 + 0.1 * rng.random(20)) % L
+    ang = 2 * np.pi * np.arange(20) / 20
+    w.x[20:40, 1], w.x[20:40, 2] = 0.997 * R * np.cos(ang), 0.997 * R * np.sin(ang)
+    w.x[100:340] = [0.013, 2e-3, -1e-3] + 8e-4 * rng.uniform(-1, 1, (240, 3))
+    w.x[400] = w.x[399] + [0.4 * w.d[399], 0.0, 0.0]
+    say("case: p3m small mesh", mesh_x, mesh_yz, alpha_h, rmax_alpha, "fp", 8 * real_bytes)
+    sim, g = gpu_accel(w, f, real_bytes, dict(mesh_x=mesh_x, mesh_yz=mesh_yz, alpha_h=alpha_h, rmax_alpha=rmax_alpha))
+    mesh = op3m.Mesh(R, L, mesh_x, mesh_yz, alpha_h, rmax_alpha)
+    S = op3m.p3m_sums(mesh, g["x"], w.sample_params[0, 0] * w.qbase, w.d)
+    a_ora = accel_from_sums(w.params, w.sample_params, w.qbase, w.d, S)
+    ora = OracleSim(w.params, f, g["x"], w.d, w.qbase, w.offsets, w.sample_params, evaluate=False)
+    tg = np.arange(w.n_particles)
+    e = np.linalg.norm(g["a"] - a_ora, axis=1) / coulomb_magnitude_sum(ora, tg)
+    say("per particle: max", e.max(), "median", np.median(e))
+    if real_bytes == 8:
+        assert e.max() < 1e-9
+    else:
+        assert np.all(e <= p3m_fp32_bound(w, nearest_distance(ora, tg)))
+
+
+@pytest.mark.parametrize("fine,coarse,alpha_h", [((1024, 16), (64, 16), 0.5), ((16, 512), (16, 64), 1.0)])
+def test_p3m_longest_lines(fine, coarse, alpha_h):
+    """Lines of 1,024 points along x and across the section (the larger spacing, and so the splitting, is
+    that of a coarse mesh in the other direction): both forms agree to the FP32 bound of the mesh part
+    (2e-6 of sum |a_ij|, the nearest pair's share aside) and with the coarse mesh to its discretisation."""
+    from tests.oracle_pool import coulomb_magnitude_sum, nearest_distance
+    from oracle.sim import OracleSim
+    w = make_workload("single-65k", n=400, field_n=16, **COULOMB_ONLY)
+    f = w.field()
+    say("case: p3m longest lines", fine)
+    a = {}
+    for key, mesh, rb in (("64", fine, 8), ("32", fine, 4), ("coarse", coarse, 8)):
+        sim, g = gpu_accel(w, f, rb, dict(mesh_x=mesh[0], mesh_yz=mesh[1], alpha_h=alpha_h, rmax_alpha=3.0))
+        a[key] = g["a"].astype(np.float64)
+        sim.close()
+    ora = OracleSim(w.params, f, w.x, w.d, w.qbase, w.offsets, w.sample_params, evaluate=False)
+    tg = np.arange(w.n_particles)
+    scale = coulomb_magnitude_sum(ora, tg)
+    e = np.linalg.norm(a["32"] - a["64"], axis=1) / scale
+    say("FP32 against FP64", e.max(), "against the coarse mesh", rel_rms(a["64"], a["coarse"]))
+    assert np.all(e <= p3m_fp32_bound(w, nearest_distance(ora, tg)))
+    assert rel_rms(a["64"], a["coarse"]) < 1e-2
