@@ -824,6 +824,7 @@ constexpr int kSrCluster = 8;                     // FP32 form: targets of one w
 constexpr int kSrSlices = 64 / kSrCluster;        // lanes per target
 constexpr int kSrRounds = 64;                     // clusters per wave and staging pass
 constexpr int kSrList = 448;                      // entries of a wave's source list
+constexpr int kSrAhead = 2;                       // entries a lane takes side by side
 
 // Short-range force profile g(s) = erfc(s) + (2 s / sqrt(pi)) exp(-s^2), s = alpha r, so that the
 // short-range force of a non-overlapping pair is q g(alpha r) r_vec / r^3; tabulated on
@@ -978,8 +979,12 @@ __global__ __launch_bounds__(kSrLanes) void k_p3m_short_f64(State<double> st, Ph
 // the tabulated profile from a copy of the table in LDS; overlapping pairs, which are rare, take
 // the exact clamp.  The list holds byte offsets of the staged records and is padded with a far,
 // uncharged dummy record (it adds an exact zero), so that every lane of the wave runs the same
-// iterations; the loop loads the next list entries and their records while it evaluates the
-// current ones.
+// iterations; the loop evaluates two entries per lane side by side, without a branch between them,
+// and loads the next two and their records meanwhile.  Bound by vector issue and LDS latency (VALU
+// busy 80 to 90 %): with a test per entry whether any lane reaches it, the branches kept the two
+// entries' roots and table reads apart (2^20 particles 1,453 us, now 1,330; 65,536 113, now 101).
+// Three or four entries lose more to the list's padding than they overlap.  The sums keep their order:
+// every change of it moves a few close pairs of a long run by more than rounding.
 __global__ __launch_bounds__(kSrLanes) __attribute__((amdgpu_waves_per_eu(6, 8))) void k_p3m_short_f32(State<float> st, Phys ph, P3mDev m,
                                                             const int32_t *__restrict__ starts,
                                                             const int32_t *__restrict__ sorted,
@@ -1077,54 +1082,75 @@ __global__ __launch_bounds__(kSrLanes) __attribute__((amdgpu_waves_per_eu(6, 8))
             wl[cnt + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u))] =
                 (uint16_t)(e * sizeof(float4));
           cnt += __builtin_popcountll(mask);
-          if (cnt <= kSrList - 64 - 4 * kSrSlices && e0 + 64 < n) continue;
+          if (cnt <= kSrList - 64 - 2 * kSrAhead * kSrSlices && e0 + 64 < n) continue;
           // pair the cluster with the listed sources, then empty the list: iterations of 8 entries,
-          // taken two at a time and loaded two iterations ahead, so the list is padded with 32
-          // dummy entries (every entry read lies below cnt + 32)
+          // taken kSrAhead at a time and loaded as many ahead, so the list is padded with dummy entries
+          // for two such groups (every entry read lies below cnt + 16 kSrAhead)
           const int iters = (cnt + kSrSlices - 1) / kSrSlices;
-          if (lane < 4 * kSrSlices) wl[cnt + lane] = (uint16_t)(CAP * sizeof(float4));
+          for (int k = lane; k < 2 * kSrAhead * kSrSlices; k += 64) wl[cnt + k] = (uint16_t)(CAP * sizeof(float4));
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
           __builtin_amdgcn_wave_barrier();
           __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-          auto pair = [&](const float4 cur, uint32_t off) {
-            // r2 carries 1e-20 (below the rounding of any r2 >= 1, i.e. of any two distinct
-            // positions) so that r = 0 (the target itself) gives a finite f times dx = 0
-            const float dx = (float)(int32_t)(mx - __float_as_uint(cur.x)) * kx;
-            const float dy = me.y - cur.y;
-            const float dz = me.z - cur.z;
-            const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, 1e-20f)));
-            if (!__builtin_amdgcn_ballot_w64(r2 < skip2q)) return;   // no lane within r_max
-            const float inv = __builtin_amdgcn_rsqf(r2);
-            const float rr = r2 * inv;
-            const float u = fminf(rr * tq, (float)kSrTable);   // u >= kSrTable: beyond r_max, entry (0, 0)
-            const float2 tv = stab[(int)u];
-            float f = cur.w * fmaf(__builtin_amdgcn_fractf(u), tv.y, tv.x) * ((inv * inv) * inv);
-            if (__builtin_amdgcn_ballot_w64(r2 < near2q)) {
-              // a pair of this source may overlap: clamped Coulomb minus the erf field, exactly
-              const float dij = rad[t0 + ti] + srad[off / sizeof(float4)];
-              if (r2 > 1e-20f && rr < dij) {
-                // 1/r = inv and 1/r^2 = inv^2 (from the rsq above, 1 ulp)
-                const float gg = c2q * expf(-aq * aq * r2) * inv;
-                f = cur.w * (1.0f / (dij * dij) - (erff(aq * rr) * (inv * inv) - gg)) * inv;
+          auto rec_at = [&](uint32_t off) { return *(const float4 *)((const char *)src + off); };
+          uint32_t on[kSrAhead];
+          float4 sn[kSrAhead];
+#pragma unroll
+          for (int p = 0; p < kSrAhead; ++p) {
+            on[p] = wl[p * kSrSlices + sl];
+            sn[p] = rec_at(on[p]);
+          }
+          for (int k = 0; k < iters; k += kSrAhead) {
+            // kSrAhead pairs a lane side by side, without a branch between them, so that their roots and
+            // table reads overlap
+            float dx[kSrAhead], dy[kSrAhead], dz[kSrAhead], q[kSrAhead], r2[kSrAhead], inv[kSrAhead], u[kSrAhead];
+            float2 tv[kSrAhead];
+            uint32_t off[kSrAhead];
+            float least = 3.0e38f;
+#pragma unroll
+            for (int p = 0; p < kSrAhead; ++p) {
+              // r2 carries 1e-20 (below the rounding of any r2 >= 1, i.e. of any two distinct
+              // positions) so that r = 0 (the target itself) gives a finite f times dx = 0
+              dx[p] = (float)(int32_t)(mx - __float_as_uint(sn[p].x)) * kx;
+              dy[p] = me.y - sn[p].y;
+              dz[p] = me.z - sn[p].z;
+              q[p] = sn[p].w;
+              off[p] = on[p];
+              r2[p] = fmaf(dx[p], dx[p], fmaf(dy[p], dy[p], fmaf(dz[p], dz[p], 1e-20f)));
+              least = fminf(least, r2[p]);
+            }
+#pragma unroll
+            for (int p = 0; p < kSrAhead; ++p) {
+              on[p] = wl[(k + kSrAhead + p) * kSrSlices + sl];
+              sn[p] = rec_at(on[p]);
+            }
+#pragma unroll
+            for (int p = 0; p < kSrAhead; ++p) {
+              inv[p] = __builtin_amdgcn_rsqf(r2[p]);
+              u[p] = fminf(r2[p] * inv[p] * tq, (float)kSrTable);   // u >= kSrTable: beyond r_max, entry (0, 0)
+              tv[p] = stab[(int)u[p]];
+            }
+            float f[kSrAhead];
+#pragma unroll
+            for (int p = 0; p < kSrAhead; ++p)
+              f[p] = q[p] * fmaf(__builtin_amdgcn_fractf(u[p]), tv[p].y, tv[p].x) * ((inv[p] * inv[p]) * inv[p]);
+            if (__builtin_amdgcn_ballot_w64(least < near2q)) {
+#pragma unroll
+              for (int p = 0; p < kSrAhead; ++p) {
+                // a pair may overlap: clamped Coulomb minus the erf field, exactly
+                const float dij = rad[t0 + ti] + srad[off[p] / sizeof(float4)], rr = r2[p] * inv[p];
+                if (r2[p] > 1e-20f && rr < dij) {
+                  // 1/r = inv and 1/r^2 = inv^2 (from the rsq above, 1 ulp)
+                  const float gg = c2q * expf(-aq * aq * r2[p]) * inv[p];
+                  f[p] = q[p] * (1.0f / (dij * dij) - (erff(aq * rr) * (inv[p] * inv[p]) - gg)) * inv[p];
+                }
               }
             }
-            sx = fmaf(f, dx, sx);
-            sy = fmaf(f, dy, sy);
-            sz = fmaf(f, dz, sz);
-          };
-          auto rec_at = [&](uint32_t off) { return *(const float4 *)((const char *)src + off); };
-          uint32_t oa = wl[sl], ob = wl[kSrSlices + sl];
-          float4 sa = rec_at(oa), sb = rec_at(ob);
-          for (int k = 0; k < iters; k += 2) {
-            const uint32_t na = wl[(k + 2) * kSrSlices + sl], nb = wl[(k + 3) * kSrSlices + sl];
-            const float4 ca = sa, cb4 = sb;
-            const uint32_t pa = oa, pb = ob;
-            sa = rec_at(na);
-            sb = rec_at(nb);
-            oa = na;
-            ob = nb;
-            pair(ca, pa);
-            if (k + 1 < iters) pair(cb4, pb);
+#pragma unroll
+            for (int p = 0; p < kSrAhead; ++p) {
+              sx = fmaf(f[p], dx[p], sx);
+              sy = fmaf(f[p], dy[p], sy);
+              sz = fmaf(f[p], dz[p], sz);
+            }
           }
           cnt = 0;
           __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
