@@ -23,6 +23,11 @@ constexpr int kSymTileMin = 256;       // smallest symmetric pair-kernel item (6
 constexpr int kP3mImages = 256;        // x images summed into the P3M Green's function
 constexpr int64_t kMaxItems = 1 << 22; // largest symmetric item list a layout reserves room for (32 B each)
 constexpr int kSimds = 1024;           // 256 CUs x 4
+constexpr int kForkBlocks = 2000;      // a step of more 64 x 64 blocks of pairs runs its forces on two branches
+// Steps per captured graph, used by calls of kBatchFrom steps and more.  It saves the gap between graphs and,
+// without a storage reorder, a launch per step (1,024 particles in FP64: 37 us a step alone, 29.7 in fours,
+// 28.8 in eights) and costs its capture (40 us more than one step's for four, 65 for eight).
+constexpr int kBatch = 4, kBatchFrom = 16;
 // FP32 defaults: the symmetric kernel (default_sym), or the one-sided kernel where the layout has too
 // many items
 const CoulombConfig kDefaultOneSided{1, 8, 32, true};
@@ -107,7 +112,7 @@ struct depo_ctx {
   OrderScratch<double> od{};
   int order_every = 0;        // steps between storage reorders (0: never)
   // captured step graph
-  hipGraphExec_t gexec = nullptr;
+  hipGraphExec_t gexec = nullptr, gexec_batch = nullptr;   // one step; kBatch steps
   hipStream_t cap_stream = nullptr;
   hipStream_t cap_side = nullptr;               // the graph's short-range branch
   hipEvent_t ev_fork = nullptr, ev_join = nullptr;
@@ -133,7 +138,8 @@ struct depo_ctx {
   }
   void drop_graph() {
     if (gexec) hipGraphExecDestroy(gexec);
-    gexec = nullptr;
+    if (gexec_batch) hipGraphExecDestroy(gexec_batch);
+    gexec = gexec_batch = nullptr;
   }
 };
 
@@ -468,79 +474,101 @@ int prepare_mode(const depo_ctx *ctx) {
 // The storage reorder kernels of a step (they act only on the steps that follow a multiple of
 // order_every steps).  Not in the smoothed-tally mode, whose adjoint stores states in one order,
 // and only with a cell list, which the short-range forces build every step.
-template <class Real> void enqueue_order(depo_ctx *ctx, hipStream_t s) {
-  if (ctx->order_every <= 0 || !short_range_on(ctx) || (ctx->p.flags & DEPO_SOFT_TALLY) || ctx->N <= 0) return;
-  launch_order<Real>(state<Real>(ctx), order_scratch<Real>(ctx), (int)ctx->N, ctx->n_cells, ctx->order_every, s);
+bool reorders(const depo_ctx *ctx) {
+  return ctx->order_every > 0 && short_range_on(ctx) && !(ctx->p.flags & DEPO_SOFT_TALLY) && ctx->N > 0;
+}
+template <class Real> void enqueue_order(depo_ctx *ctx, hipStream_t s, int ahead = 0) {
+  if (reorders(ctx))
+    launch_order<Real>(state<Real>(ctx), order_scratch<Real>(ctx), (int)ctx->N, ctx->n_cells, ctx->order_every, ahead, s);
 }
 
-template <class Real> void enqueue_step(depo_ctx *ctx, hipStream_t s) {
+// The forces of a step: the direct Coulomb sums and, on stream b if it is another one, the cell build and
+// the short-range forces (which touch disjoint buffers), so that the O(N) branch fills the pair kernel's
+// tail.  Returns the k_finish mode bit of the pair sums in pair_mode.
+template <class Real> hipError_t enqueue_step_forces(depo_ctx *ctx, hipStream_t a, hipStream_t b, int &pair_mode) {
   const State<Real> &st = state<Real>(ctx);
-  enqueue_order<Real>(ctx, s);
-  launch_prepare<Real>(st, ctx->ph, prepare_mode(ctx) | P_KICK_DRIFT, s);
-  if (short_range_on(ctx)) launch_cells<Real>(st, ctx->ph, ctx->n_cells, (ctx->n_cells + 1023) / 1024, s);
-  const int pair_mode = enqueue_coulomb<Real>(ctx, s, true);
-  if (short_range_on(ctx)) launch_short_range<Real>(st, ctx->ph, ctx->n_cells, s);
-  launch_finish<Real>(st, ctx->ph, F_KICK | pair_mode, s);
+  hipError_t e = hipSuccess;
+  if (b != a) {
+    if ((e = hipEventRecord(ctx->ev_fork, a)) != hipSuccess) return e;
+    if ((e = hipStreamWaitEvent(b, ctx->ev_fork, 0)) != hipSuccess) return e;
+  }
+  if (short_range_on(ctx)) launch_cells<Real>(st, ctx->ph, ctx->n_cells, (ctx->n_cells + 1023) / 1024, b);
+  if (b != a) {
+    launch_short_range<Real>(st, ctx->ph, ctx->n_cells, b);
+    if ((e = hipEventRecord(ctx->ev_join, b)) != hipSuccess) return e;
+  }
+  pair_mode = enqueue_coulomb<Real>(ctx, a, true);
+  if (b != a) return hipStreamWaitEvent(a, ctx->ev_join, 0);
+  if (short_range_on(ctx)) launch_short_range<Real>(st, ctx->ph, ctx->n_cells, a);
+  return hipSuccess;
 }
 
-// One step as a graph with two branches after prepare: the direct Coulomb sums, and the cell
-// build + short-range forces (which touch disjoint buffers), joined before finish, so that the
-// O(N) branch fills the pair kernel's tail.
-template <class Real> hipError_t capture_forked_step(depo_ctx *ctx) {
+// `steps` steps on stream a (b: see above).  Without a storage reorder between them, the second half of a step and
+// the first of the next are one kernel.
+template <class Real> hipError_t enqueue_steps(depo_ctx *ctx, hipStream_t a, hipStream_t b, int steps) {
   const State<Real> &st = state<Real>(ctx);
-  hipStream_t a = ctx->cap_stream, b = ctx->cap_side;
-  enqueue_order<Real>(ctx, a);
-  launch_prepare<Real>(st, ctx->ph, prepare_mode(ctx) | P_KICK_DRIFT, a);
-  hipError_t e = hipEventRecord(ctx->ev_fork, a);
-  if (e == hipSuccess) e = hipStreamWaitEvent(b, ctx->ev_fork, 0);
-  if (e != hipSuccess) return e;
-  launch_cells<Real>(st, ctx->ph, ctx->n_cells, (ctx->n_cells + 1023) / 1024, b);
-  launch_short_range<Real>(st, ctx->ph, ctx->n_cells, b);
-  if ((e = hipEventRecord(ctx->ev_join, b)) != hipSuccess) return e;
-  const int pair_mode = enqueue_coulomb<Real>(ctx, a, true);
-  if ((e = hipStreamWaitEvent(a, ctx->ev_join, 0)) != hipSuccess) return e;
-  launch_finish<Real>(st, ctx->ph, F_KICK | pair_mode, a);
+  const int prepare = prepare_mode(ctx) | P_KICK_DRIFT;
+  const bool fuse = !reorders(ctx);
+  for (int k = 0; k < steps; ++k) {
+    if (k == 0 || !fuse) {
+      enqueue_order<Real>(ctx, a, k);
+      launch_prepare<Real>(st, ctx->ph, prepare, a, k);
+    }
+    int pair_mode = 0;
+    if (hipError_t e = enqueue_step_forces<Real>(ctx, a, b, pair_mode); e != hipSuccess) return e;
+    const bool last = k + 1 == steps;
+    if (!last && fuse)
+      launch_finish_prepare<Real>(st, ctx->ph, F_KICK | pair_mode, prepare, k + 1, a);
+    else
+      launch_finish<Real>(st, ctx->ph, F_KICK | pair_mode, a, last ? steps : 0);
+  }
   return hipGetLastError();
+}
+
+// Captures `steps` steps.  Two branches pay where the pair sums take far longer than their join and fork
+// (the P3M pipeline has cell passes of its own: one branch).  Steps in FP32 with one and with two branches, us:
+// 1,024 particles 28.6, 30.9; 3,001 33.9, 34.2; 4,000 (2,016 blocks of pairs) 38.0, 36.6; 5,600 42.7, 39.6;
+// 16,000 106, 97; in FP64 the same way.
+template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGraphExec_t &exec) {
+  if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
+  const bool fork = short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
+                    count_items(ctx->off, 64, 1) > kForkBlocks;
+  if (fork && !ctx->cap_side) {
+    HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_side, hipStreamNonBlocking));
+    HIP_TRY(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
+  }
+  hipGraph_t g = nullptr;
+  HIP_TRY(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeRelaxed));
+  const hipError_t e = enqueue_steps<Real>(ctx, ctx->cap_stream, fork ? ctx->cap_side : ctx->cap_stream, steps);
+  const hipError_t e2 = hipStreamEndCapture(ctx->cap_stream, &g);
+  if (e != hipSuccess || e2 != hipSuccess) {
+    if (g) hipGraphDestroy(g);
+    return ctx->fail(DEPO_E_HIP, "step graph capture failed: %s", hipGetErrorString(e != hipSuccess ? e : e2));
+  }
+  const hipError_t e3 = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+  hipGraphDestroy(g);
+  if (e3 != hipSuccess) {
+    exec = nullptr;
+    return ctx->fail(DEPO_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e3));
+  }
+  return DEPO_OK;
 }
 
 template <class Real> depo_status run_steps(depo_ctx *ctx, int n, hipStream_t s) {
   if (n == 0) return DEPO_OK;
   if (ctx->use_graph) {
-    if (!ctx->gexec) {
-      if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
-      // the P3M pipeline has cell passes of its own: it stays on one branch
-      const bool fork = short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use;
-      if (fork && !ctx->cap_side) {
-        HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_side, hipStreamNonBlocking));
-        HIP_TRY(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
-        HIP_TRY(hipEventCreateWithFlags(&ctx->ev_join, hipEventDisableTiming));
-      }
-      hipGraph_t g = nullptr;
-      HIP_TRY(hipStreamBeginCapture(ctx->cap_stream, hipStreamCaptureModeRelaxed));
-      hipError_t e = hipSuccess;
-      if (fork)
-        e = capture_forked_step<Real>(ctx);
-      else {
-        enqueue_step<Real>(ctx, ctx->cap_stream);
-        e = hipGetLastError();
-      }
-      hipError_t e2 = hipStreamEndCapture(ctx->cap_stream, &g);
-      if (e != hipSuccess || e2 != hipSuccess) {
-        if (g) hipGraphDestroy(g);
-        return ctx->fail(DEPO_E_HIP, "step graph capture failed: %s",
-                         hipGetErrorString(e != hipSuccess ? e : e2));
-      }
-      hipError_t e3 = hipGraphInstantiate(&ctx->gexec, g, nullptr, nullptr, 0);
-      hipGraphDestroy(g);
-      if (e3 != hipSuccess) {
-        ctx->gexec = nullptr;
-        return ctx->fail(DEPO_E_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e3));
-      }
+    int k = 0;
+    if (n >= kBatchFrom) {
+      if (!ctx->gexec_batch)
+        if (depo_status e = capture_steps<Real>(ctx, kBatch, ctx->gexec_batch); e != DEPO_OK) return e;
+      for (; k + kBatch <= n; k += kBatch) HIP_TRY(hipGraphLaunch(ctx->gexec_batch, s));
     }
-    for (int k = 0; k < n; ++k) HIP_TRY(hipGraphLaunch(ctx->gexec, s));
+    if (k < n && !ctx->gexec)
+      if (depo_status e = capture_steps<Real>(ctx, 1, ctx->gexec); e != DEPO_OK) return e;
+    for (; k < n; ++k) HIP_TRY(hipGraphLaunch(ctx->gexec, s));
   } else {
-    for (int k = 0; k < n; ++k) enqueue_step<Real>(ctx, s);
-    HIP_TRY(hipGetLastError());
+    for (int k = 0; k < n; ++k) HIP_TRY(enqueue_steps<Real>(ctx, s, s, 1));
   }
   ctx->nstep += n;
   return DEPO_OK;

@@ -26,8 +26,8 @@ constexpr int kThreads = 256;
 constexpr int kPer = 4;                       // slots per thread, kThreads apart (consecutive lanes, consecutive slots)
 constexpr int kBlock = kThreads * kPer;       // slots per block of the count and scatter passes
 
-__device__ __forceinline__ bool due(const int32_t *nstep, int every) {
-  const int n = *nstep;
+__device__ __forceinline__ bool due(const int32_t *nstep, int every, int ahead) {
+  const int n = *nstep + ahead;
   return every > 0 && n > 0 && n % every == 0;
 }
 
@@ -50,8 +50,8 @@ __device__ __forceinline__ int block_scan(int v, int *sh, int &total) {
 
 // pos[i] = position of alive particle i in the cell list
 template <class Real>
-__global__ __launch_bounds__(kThreads) void k_order_inverse(State<Real> st, int n_cells, int every) {
-  if (!due(st.nstep, every)) return;
+__global__ __launch_bounds__(kThreads) void k_order_inverse(State<Real> st, int n_cells, int every, int ahead) {
+  if (!due(st.nstep, every, ahead)) return;
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= st.cell_start[n_cells]) return;
   st.cell_of[st.cell_idx[k]] = k;
@@ -59,8 +59,8 @@ __global__ __launch_bounds__(kThreads) void k_order_inverse(State<Real> st, int 
 
 // removed particles per block of kBlock slots
 template <class Real>
-__global__ __launch_bounds__(kThreads) void k_order_count(State<Real> st, int n, int every) {
-  if (!due(st.nstep, every)) return;
+__global__ __launch_bounds__(kThreads) void k_order_count(State<Real> st, int n, int every, int ahead) {
+  if (!due(st.nstep, every, ahead)) return;
   __shared__ int sh[kThreads];
   const int base = blockIdx.x * kBlock + threadIdx.x;
   int c = 0;
@@ -76,8 +76,8 @@ __global__ __launch_bounds__(kThreads) void k_order_count(State<Real> st, int n,
 
 // exclusive scan of the block counts (one workgroup)
 template <class Real>
-__global__ __launch_bounds__(kThreads) void k_order_top(State<Real> st, int nb, int every) {
-  if (!due(st.nstep, every)) return;
+__global__ __launch_bounds__(kThreads) void k_order_top(State<Real> st, int nb, int every, int ahead) {
+  if (!due(st.nstep, every, ahead)) return;
   __shared__ int sh[kThreads];
   int carry = 0;
   for (int b0 = 0; b0 < nb; b0 += kThreads) {
@@ -92,8 +92,9 @@ __global__ __launch_bounds__(kThreads) void k_order_top(State<Real> st, int nb, 
 
 // new slot of every particle, and its state into the scratch copy there
 template <class Real>
-__global__ __launch_bounds__(kThreads) void k_order_scatter(State<Real> st, OrderScratch<Real> sc, int n, int every) {
-  if (!due(st.nstep, every)) return;
+__global__ __launch_bounds__(kThreads) void k_order_scatter(State<Real> st, OrderScratch<Real> sc, int n, int every,
+                                                            int ahead) {
+  if (!due(st.nstep, every, ahead)) return;
   __shared__ int sh[kThreads];
   const int base = blockIdx.x * kBlock + threadIdx.x;
   int run = st.scan_part[blockIdx.x];   // removed particles in the slots before this row of the block
@@ -132,8 +133,9 @@ __global__ __launch_bounds__(kThreads) void k_order_scatter(State<Real> st, Orde
 }
 
 template <class Real>
-__global__ __launch_bounds__(kThreads) void k_order_copy(State<Real> st, OrderScratch<Real> sc, int n, int every) {
-  if (!due(st.nstep, every)) return;
+__global__ __launch_bounds__(kThreads) void k_order_copy(State<Real> st, OrderScratch<Real> sc, int n, int every,
+                                                         int ahead) {
+  if (!due(st.nstep, every, ahead)) return;
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   st.px[k] = sc.px[k]; st.py[k] = sc.py[k]; st.pz[k] = sc.pz[k];
@@ -149,18 +151,21 @@ __global__ __launch_bounds__(kThreads) void k_order_copy(State<Real> st, OrderSc
 }  // namespace
 
 template <class Real>
-void launch_order(const State<Real> &st, const OrderScratch<Real> &sc, int n, int n_cells, int every, hipStream_t s) {
+void launch_order(const State<Real> &st, const OrderScratch<Real> &sc, int n, int n_cells, int every, int ahead,
+                  hipStream_t s) {
   if (n <= 0 || every <= 0) return;
   const unsigned g = (unsigned)((n + kThreads - 1) / kThreads);
   const int nb = (n + kBlock - 1) / kBlock;
-  hipLaunchKernelGGL((k_order_inverse<Real>), dim3(g), dim3(kThreads), 0, s, st, n_cells, every);
-  hipLaunchKernelGGL((k_order_count<Real>), dim3((unsigned)nb), dim3(kThreads), 0, s, st, n, every);
-  hipLaunchKernelGGL((k_order_top<Real>), dim3(1), dim3(kThreads), 0, s, st, nb, every);
-  hipLaunchKernelGGL((k_order_scatter<Real>), dim3((unsigned)nb), dim3(kThreads), 0, s, st, sc, n, every);
-  hipLaunchKernelGGL((k_order_copy<Real>), dim3(g), dim3(kThreads), 0, s, st, sc, n, every);
+  hipLaunchKernelGGL((k_order_inverse<Real>), dim3(g), dim3(kThreads), 0, s, st, n_cells, every, ahead);
+  hipLaunchKernelGGL((k_order_count<Real>), dim3((unsigned)nb), dim3(kThreads), 0, s, st, n, every, ahead);
+  hipLaunchKernelGGL((k_order_top<Real>), dim3(1), dim3(kThreads), 0, s, st, nb, every, ahead);
+  hipLaunchKernelGGL((k_order_scatter<Real>), dim3((unsigned)nb), dim3(kThreads), 0, s, st, sc, n, every, ahead);
+  hipLaunchKernelGGL((k_order_copy<Real>), dim3(g), dim3(kThreads), 0, s, st, sc, n, every, ahead);
 }
 
-template void launch_order<float>(const State<float> &, const OrderScratch<float> &, int, int, int, hipStream_t);
-template void launch_order<double>(const State<double> &, const OrderScratch<double> &, int, int, int, hipStream_t);
+template void launch_order<float>(const State<float> &, const OrderScratch<float> &, int, int, int, int,
+                                  hipStream_t);
+template void launch_order<double>(const State<double> &, const OrderScratch<double> &, int, int, int, int,
+                                   hipStream_t);
 
 }  // namespace depo

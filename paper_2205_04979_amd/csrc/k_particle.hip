@@ -61,12 +61,11 @@ __device__ __forceinline__ void gather(const typename Prec<Real>::Vec4 *__restri
 // First half of a step (mode P_KICK_DRIFT): half kick, drift, wall test.  Always
 // (re)writes the Coulomb source record and, with P_CELLS, the cell id and the
 // cell histogram of the short-range search.
+// ahead: steps done since the counter was last brought up to date.
 template <class Real>
-__global__ __launch_bounds__(256) void k_prepare(State<Real> st, Phys ph, int mode) {
+__device__ __forceinline__ void prepare_particle(const State<Real> &st, const Phys &ph, int mode, int ahead, int i) {
   using Pos = typename Prec<Real>::Pos;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ph.N) return;
-  const int step = *st.nstep + 1;
+  const int step = *st.nstep + 1 + ahead;
   bool alive = st.dep[i] == 0;
   Pos px = st.px[i], py = st.py[i], pz = st.pz[i];
   Real rx = st.rx[i], ry = st.ry[i], rz = st.rz[i];
@@ -171,6 +170,12 @@ __global__ __launch_bounds__(256) void k_prepare(State<Real> st, Phys ph, int mo
   }
 }
 
+template <class Real>
+__global__ __launch_bounds__(256) void k_prepare(State<Real> st, Phys ph, int mode, int ahead) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < ph.N) prepare_particle<Real>(st, ph, mode, ahead, i);
+}
+
 // Second half of a step (F_KICK): assemble a^{n+1} = Coulomb + short-range + wall
 // (+ body) at the new positions, gather u_f(x^{n+1}), half kick, smoothed tally.
 // Without F_KICK it only evaluates the acceleration and the fluid velocity
@@ -179,11 +184,7 @@ __global__ __launch_bounds__(256) void k_prepare(State<Real> st, Phys ph, int mo
 // else: the seed runs it before the first force evaluation, whose collision
 // damping reads the velocities of neighbours.
 template <class Real>
-__global__ __launch_bounds__(256) void k_finish(State<Real> st, Phys ph, int mode) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  // the step counter advances once per step; no thread of this kernel reads it
-  if ((mode & F_KICK) && i == 0) *st.nstep += 1;
-  if (i >= ph.N) return;
+__device__ __forceinline__ void finish_particle(const State<Real> &st, const Phys &ph, int mode, int i) {
   Real cs[3];   // Coulomb pair sums of this particle
   if constexpr (sizeof(Real) == 4) {
     if (mode & F_PAIR_SUMS) {
@@ -273,6 +274,25 @@ __global__ __launch_bounds__(256) void k_finish(State<Real> st, Phys ph, int mod
   if (!finite) atomicOr(st.err, ERR_NONFINITE);
 }
 
+// advance: steps that end here, added to the step counter (no thread of this kernel reads it).
+template <class Real>
+__global__ __launch_bounds__(256) void k_finish(State<Real> st, Phys ph, int mode, int advance) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (advance > 0 && i == 0) *st.nstep += advance;
+  if (i < ph.N) finish_particle<Real>(st, ph, mode, i);
+}
+
+// The second half of a step and the first half of the next, which touch nothing but the particle itself: one
+// launch and its gap less per step, 3 to 4 us.
+template <class Real>
+__global__ __launch_bounds__(256) void k_finish_prepare(State<Real> st, Phys ph, int finish_mode, int prepare_mode,
+                                                        int ahead) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= ph.N) return;
+  finish_particle<Real>(st, ph, finish_mode, i);
+  prepare_particle<Real>(st, ph, prepare_mode, ahead, i);
+}
+
 // Per-sample tally (Eq. 2): deposited mass/count, the alive-mass time integral
 // dt * sum_i m_i * (steps suspended), the Poisson error term and the smoothed
 // deposited mass.  One block per sample; fixed-order strided loop and tree
@@ -304,24 +324,33 @@ __global__ __launch_bounds__(256) void k_tally(State<Real> st, Phys ph, int nste
 }
 
 template <class Real>
-void launch_prepare(const State<Real> &st, const Phys &ph, int mode, hipStream_t s) {
+void launch_prepare(const State<Real> &st, const Phys &ph, int mode, hipStream_t s, int ahead) {
   if (ph.N == 0) return;
-  hipLaunchKernelGGL(k_prepare<Real>, dim3((ph.N + 255) / 256), dim3(256), 0, s, st, ph, mode);
+  hipLaunchKernelGGL(k_prepare<Real>, dim3((ph.N + 255) / 256), dim3(256), 0, s, st, ph, mode, ahead);
 }
 template <class Real>
-void launch_finish(const State<Real> &st, const Phys &ph, int mode, hipStream_t s) {
+void launch_finish_prepare(const State<Real> &st, const Phys &ph, int finish_mode, int prepare_mode, int ahead,
+                           hipStream_t s) {
+  if (ph.N == 0) return;
+  hipLaunchKernelGGL(k_finish_prepare<Real>, dim3((ph.N + 255) / 256), dim3(256), 0, s, st, ph, finish_mode,
+                     prepare_mode, ahead);
+}
+template <class Real>
+void launch_finish(const State<Real> &st, const Phys &ph, int mode, hipStream_t s, int steps) {
   hipLaunchKernelGGL(k_finish<Real>, dim3((ph.N + 255) / 256 > 0 ? (ph.N + 255) / 256 : 1), dim3(256), 0, s, st,
-                     ph, mode);
+                     ph, mode, (mode & F_KICK) ? steps : 0);
 }
 template <class Real>
 void launch_tally(const State<Real> &st, const Phys &ph, int nstep, hipStream_t s) {
   hipLaunchKernelGGL(k_tally<Real>, dim3(ph.S), dim3(256), 0, s, st, ph, nstep);
 }
 
-template void launch_prepare<float>(const State<float> &, const Phys &, int, hipStream_t);
-template void launch_prepare<double>(const State<double> &, const Phys &, int, hipStream_t);
-template void launch_finish<float>(const State<float> &, const Phys &, int, hipStream_t);
-template void launch_finish<double>(const State<double> &, const Phys &, int, hipStream_t);
+template void launch_prepare<float>(const State<float> &, const Phys &, int, hipStream_t, int);
+template void launch_finish_prepare<float>(const State<float> &, const Phys &, int, int, int, hipStream_t);
+template void launch_prepare<double>(const State<double> &, const Phys &, int, hipStream_t, int);
+template void launch_finish_prepare<double>(const State<double> &, const Phys &, int, int, int, hipStream_t);
+template void launch_finish<float>(const State<float> &, const Phys &, int, hipStream_t, int);
+template void launch_finish<double>(const State<double> &, const Phys &, int, hipStream_t, int);
 template void launch_tally<float>(const State<float> &, const Phys &, int, hipStream_t);
 template void launch_tally<double>(const State<double> &, const Phys &, int, hipStream_t);
 

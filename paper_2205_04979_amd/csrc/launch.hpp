@@ -13,14 +13,23 @@ enum : int { P_KICK_DRIFT = 1, P_COULOMB = 2, P_CELLS = 4, P_SEED = 8 };
 // the pieces' partial sums
 enum : int { F_KICK = 1, F_V_FROM_FLUID = 2, F_FLUID_ONLY = 4, F_PAIR_SUMS = 8 };
 
-template <class Real> void launch_prepare(const State<Real> &st, const Phys &ph, int mode, hipStream_t s);
-template <class Real> void launch_finish(const State<Real> &st, const Phys &ph, int mode, hipStream_t s);
+// A batch of steps brings the device's step counter up to date in its last k_finish (by `steps`); its other
+// kernels that need the step's number are told how many steps `ahead` of the counter they are.
+template <class Real>
+void launch_prepare(const State<Real> &st, const Phys &ph, int mode, hipStream_t s, int ahead = 0);
+template <class Real>
+void launch_finish(const State<Real> &st, const Phys &ph, int mode, hipStream_t s, int steps = 1);
+// k_finish of one step and k_prepare of the next, `ahead` steps after the counter
+template <class Real>
+void launch_finish_prepare(const State<Real> &st, const Phys &ph, int finish_mode, int prepare_mode, int ahead,
+                           hipStream_t s);
 template <class Real> void launch_tally(const State<Real> &st, const Phys &ph, int nstep, hipStream_t s);
 
 // Storage order: at the start of a step that follows a multiple of `every` steps (decided on the
 // device from the step counter), permute the per-particle state into the order of the last cell list.
 template <class Real>
-void launch_order(const State<Real> &st, const OrderScratch<Real> &sc, int n, int n_cells, int every, hipStream_t s);
+void launch_order(const State<Real> &st, const OrderScratch<Real> &sc, int n, int n_cells, int every, int ahead,
+                  hipStream_t s);
 
 // Cell list: scan of the histogram, scatter, in-cell ordering, short-range forces.
 template <class Real>

@@ -405,6 +405,6 @@ def test_fp32_symmetric_adjoint_shapes_on_uneven_samples(cfg):
     big = np.abs(g["fp64"]) > 1e-3 * np.abs(g["fp64"]).max()
     assert big[-1]
     for key, tol in (("one", 1e-5), ("fp64", 1e-3)):
-        dev = (np.abs(g["this"] - g[key]) / np.abs(g[key]))[big].max()
+        dev = (np.abs(g["this"] - g[key])[big] / np.abs(g[key])[big]).max()
         say("against", key, dev, g["this"].tolist())
         assert dev < tol

@@ -952,3 +952,36 @@ def test_cell_list_in_one_kernel(real_bytes, sizes, crowd):
     assert top > 0 and worst <= (1e-4 if real_bytes == 4 else 1e-9) * top
     sim.eval_accel()
     assert np.array_equal(g0["a"], sim.read()["a"])
+
+
+@pytest.mark.parametrize("real_bytes", [4, 8])
+@pytest.mark.parametrize("n,reorder", [(700, 0), (700, 3), (6000, 0)])
+def test_batched_steps_equal_single_ones(real_bytes, n, reorder):
+    """Long calls replay graphs of several steps (the halves of consecutive steps in one kernel where no storage
+    reorder comes between; one branch for small layouts, two for larger ones).  Calls on both sides of every
+    batch length, with removals at the wall in between, leave bitwise the state, the removal steps and the
+    tallies of the same number of single direct steps."""
+    w = make_workload("single-65k", n=n, field_n=32)
+    f = w.field()
+    x, d = w.x.copy(), w.d
+    rng = np.random.default_rng(3)
+    er = rng.normal(size=(40, 2))
+    er /= np.linalg.norm(er, axis=1)[:, None]
+    x[:40, 1:] = er * (w.params["R"] - 0.5 * d[:40] - rng.uniform(0.0, 4e-6, 40))[:, None]
+    v0 = np.zeros((n, 3))
+    v0[:40, 1:] = 0.5 * er
+    out = []
+    for graph, calls in ((True, (15, 16, 1, 21, 4, 37)), (False, (94,))):
+        sim, _ = seeded_pair(w.params, f, x, d, w.qbase, w.offsets, w.sample_params, real_bytes, v0=v0, oracle=False)
+        cfg = (1, 4, 64, 2) if real_bytes == 4 else (1, 4, 16)
+        sim.set_kernel_config(*cfg, use_graph=graph)
+        sim.set_reorder(reorder)
+        sim.seed(w.sample_params, x, d, w.qbase, v=v0)
+        for c in calls:
+            sim.step(c)
+        out.append((sim.read(), sim.tally()))
+    say("case: batched steps", n, reorder, "fp", 8 * real_bytes, "removed", int((out[0][0]["dep_step"] > 0).sum()))
+    assert len(set(out[0][0]["dep_step"][:40].tolist())) > 3
+    for k in ("x", "v", "a", "dep_step", "neighbours"):
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert out[0][1] == out[1][1]
