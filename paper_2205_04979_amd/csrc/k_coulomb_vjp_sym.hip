@@ -37,6 +37,7 @@ namespace {
 template <int CTRL> __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(v), __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
+template <int IPL, int W> constexpr bool kCombine = IPL <= 2 && W > 1;   // as in the forward kernel
 constexpr int kStage = 2;          // rounds of sources held in LDS at a time (a power of two; 8 KB, for 16 waves a CU)
 constexpr int kWaveRol1 = 0x134;   // lane l receives the value of lane (l + 1) mod 64
 
@@ -137,7 +138,7 @@ template <int IPL, int W, bool REACT>
 __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *__restrict__ rec,
                                          const float *__restrict__ jr, double *__restrict__ ax,
                                          double *__restrict__ ay, double *__restrict__ az, float near2,
-                                         JAdj<float> *src) {
+                                         JAdj<float> *src, float (*comb)[3][W][64]) {
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
 
@@ -283,7 +284,23 @@ __device__ __forceinline__ void vjp_item(const SymItem &it, const JAdj<float> *_
       hy[k] += (double)sy[k];
       hz[k] += (double)sz[k];
     }
-    if constexpr (REACT) {
+    if constexpr (REACT && kCombine<IPL, W>) {
+      // after 64 rotations lane l holds the reaction of source jb + l on this wave's targets: the waves'
+      // are added first (alternating buffers: one barrier a round)
+      float(*c)[W][64] = comb[(jb >> 6) & 1];
+      c[0][w][lane] = rx;
+      c[1][w][lane] = ry;
+      c[2][w][lane] = rz;
+      __syncthreads();
+      for (int e = threadIdx.x; e < 192; e += 64 * W) {
+        const int k = e >> 6, jj = jb + (e & 63);
+        if (jj >= it.jcount) continue;
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < W; ++q) v += (double)c[k][q][e & 63];
+        dadd(k == 0 ? ax : k == 1 ? ay : az, (int64_t)it.j0 + jj, v);
+      }
+    } else if constexpr (REACT) {
       // after 64 rotations lane l holds the reaction of source jb + l on this wave's targets
       if (jb + lane < it.jcount) {
         const int64_t j = (int64_t)it.j0 + jb + lane;
@@ -311,11 +328,12 @@ __global__ __launch_bounds__(64 * W) void k_coulomb_vjp_sym(const SymItem *__res
                                                             double *__restrict__ ay, double *__restrict__ az,
                                                             float near2) {
   __shared__ JAdj<float> src[128 * kStage];
+  __shared__ float comb[kCombine<IPL, W> ? 2 : 1][3][W][64];
   const SymItem it = items[blockIdx.x];
   if (it.diag)
-    vjp_item<IPL, W, false>(it, rec, jr, ax, ay, az, near2, src);
+    vjp_item<IPL, W, false>(it, rec, jr, ax, ay, az, near2, src, comb);
   else
-    vjp_item<IPL, W, true>(it, rec, jr, ax, ay, az, near2, src);
+    vjp_item<IPL, W, true>(it, rec, jr, ax, ay, az, near2, src, comb);
 }
 
 // Totals (in units of the x quantum) to x_bar contributions; the accumulators are cleared.
