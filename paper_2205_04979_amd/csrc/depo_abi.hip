@@ -362,7 +362,11 @@ CoulombConfig default_sym(const std::vector<int64_t> &off) {
   return CoulombConfig{4, 1, 64, true, true};
 }
 
-// Work items of the symmetric pair kernel, the diagonal ones first, each kind by cost.
+// Work items of the symmetric pair kernel, the diagonal ones first, each kind by cost.  Where there are enough
+// waves for four rounds an item, half of the sources after a tile go in pieces of sixteen: they start first
+// and spare additions to the accumulators, the short ones level the end (ten samples of 2,048 to
+// 32,768 particles 728 -> 703 us, 65,536 769 -> 760 us; three quarters in long pieces: 714 and 775 us).
+constexpr int64_t kLongPiece = 64 * 16;
 void build_items(const depo_ctx *ctx, int T, int rounds, std::vector<SymItem> &items) {
   std::vector<SymItem> diag, off;
   const int64_t P = 64 * (int64_t)rounds, Pd = std::min<int64_t>(P, T);
@@ -372,7 +376,10 @@ void build_items(const depo_ctx *ctx, int T, int rounds, std::vector<SymItem> &i
       const int64_t own = std::min<int64_t>(T, e - b);
       for (int64_t p = 0; p < own; p += Pd)
         diag.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)(b + p), (int32_t)std::min(Pd, own - p), s, 1, {0, 0}});
-      for (int64_t j = b + own; j < e; j += P)
+      int64_t j = b + own;
+      for (int64_t k = rounds == 4 ? (e - j) / (2 * kLongPiece) : 0; k > 0; --k, j += kLongPiece)
+        off.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)j, (int32_t)kLongPiece, s, 0, {0, 0}});
+      for (; j < e; j += P)
         off.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)j, (int32_t)std::min(P, e - j), s, 0, {0, 0}});
     }
   }
