@@ -815,6 +815,7 @@ __global__ void k_p3m_records(State<Real> st, Phys ph, const int32_t *__restrict
 constexpr int kSrLds = 65536;    // bytes of LDS for staged neighbour records (FP64 form)
 constexpr int kSrWaves = 8;      // waves per cell
 constexpr int kSrLanes = 64 * kSrWaves;
+constexpr int kSrTargets = 32;   // FP64 form: targets of a workgroup at a time
 constexpr int kSrMaxSlices = 32; // FP64 form: at most this many threads share one target
 constexpr int kSrTable = 2048;   // intervals of the tabulated short-range profile (FP32 form)
 // FP32 form: 28,000 B of staged records + 16.4 KB of table + 7 KB of source lists keep a workgroup
@@ -890,11 +891,15 @@ __device__ __forceinline__ void stage_sources(const Rec *__restrict__ rec, const
 // Short range (Coulomb with the overlap clamp minus the erf field) over nearest-image neighbours
 // closer than r_max, added to the long-range part; result in units of the x quantum.
 //
-// FP64 form: the exact expressions, in metres.  One workgroup per cell: the records of the 27
-// neighbouring cells are staged in LDS (in chunks when they exceed it); the cell's nb targets (up
-// to 512 at a time) share the 512 threads, S = 512 / nb threads per target (at most 32), and
-// thread g takes target g mod nb and every S-th staged source from slice g / nb on; the S partial
-// sums of a target are combined in FP64 in slice order.
+// FP64 form: the exact expressions, in metres.  Workgroups of a cell take kSrTargets of its targets at a time:
+// the records of the 27 neighbouring cells are staged in LDS (in chunks when they exceed it); the nb
+// targets share the 512 threads, S = 512 / nb threads per target (at most kSrMaxSlices), and thread g takes
+// target g mod nb and every S-th staged source from slice g / nb on; the S partial sums of a target are
+// combined in FP64 in slice order.  Bound by the FP64 functions of a pair (some 200 instructions) and, at
+// two workgroups a CU, their latency: sources beyond r_max (six of seven) are left out by an FP32 test
+// first, and a mesh of few cells still makes enough workgroups.  40,000 particles in 128 cells,
+// 8 steps: 45.5 -> 16.8 ms; 12,000: 7.5 -> 2.8 ms (16.8 with 32 targets at a time, 18.0 with 64, 23.1 with 128;
+// 19.2 with 64 and without the test).
 __global__ __launch_bounds__(kSrLanes) void k_p3m_short_f64(State<double> st, Phys ph, P3mDev m,
                                                             const int32_t *__restrict__ starts,
                                                             const int32_t *__restrict__ sorted,
@@ -907,14 +912,16 @@ __global__ __launch_bounds__(kSrLanes) void k_p3m_short_f64(State<double> st, Ph
   const int c = blockIdx.x;
   const int cz = c % m.ncy, cy = (c / m.ncy) % m.ncy, cx = c / (m.ncy * m.ncy);
   const int t0 = starts[c], nt = starts[c + 1] - t0;
-  if (nt == 0) return;   // uniform: the whole workgroup leaves
+  if ((int)blockIdx.y * kSrTargets >= nt) return;   // uniform: the whole workgroup leaves
   neighbour_ranges(m, starts, cx, cy, cz, rb, rn, roff);
   const int total = roff[27];
   const double ux = ph.ux, ur = ph.ur;
   const double a = m.alpha, c2 = 2.0 * m.alpha / sqrt(M_PI), rmax2 = m.rmax * m.rmax;
+  // 2^32 quanta; r_max squared with a margin far above the test's rounding
+  const float fux = (float)(ux * 0x1p32), fur = (float)(ur * 0x1p32), frmax2 = (float)(rmax2 * 1.0001);
   const bool once = total <= CAP;   // all sources fit: staged once for every target block
-  for (int tb = 0; tb < nt; tb += kSrLanes) {
-    const int nb = min(kSrLanes, nt - tb);
+  for (int tb = blockIdx.y * kSrTargets; tb < nt; tb += gridDim.y * kSrTargets) {
+    const int nb = min(kSrTargets, nt - tb);
     const int S = min(kSrLanes / nb, kSrMaxSlices);   // threads per target
     const int g = threadIdx.x;
     const bool has = g < nb * S;
@@ -923,24 +930,41 @@ __global__ __launch_bounds__(kSrLanes) void k_p3m_short_f64(State<double> st, Ph
     double sx = 0, sy = 0, sz = 0;
     for (int cb = 0; cb < total; cb += CAP) {
       const int n = min(CAP, total - cb);
-      if (!once || tb == 0) stage_sources(rec, (const float *)nullptr, rb, roff, cb, n, src, (float *)nullptr);
+      if (!once || tb == (int)blockIdx.y * kSrTargets) stage_sources(rec, (const float *)nullptr, rb, roff, cb, n, src, (float *)nullptr);
       if (!has) continue;
-      for (int e = slice; e < n; e += S) {
-        const SrRec64 s = src[e];
-        const double dx = double((int64_t)(me.x - s.x)) * ux;
-        const double dy = double(me.y - s.y) * ur;
-        const double dz = double(me.z - s.z) * ur;
-        const double r2 = dx * dx + dy * dy + dz * dz;
-        const double dij = 0.5 * (me.d + s.d);
-        double f = 0.0;
-        if (r2 < rmax2 && r2 > 0.0) {
-          const double r = sqrt(r2);
-          const double gg = c2 * exp(-a * a * r2) / r;
-          f = (r >= dij ? erfc(a * r) / r2 + gg : 1.0 / (dij * dij) - (erf(a * r) / r2 - gg)) * s.q / r;
+      // 64 sources at a time: those that may be within r_max (FP32, from the leading 32 bits of the
+      // differences), then each lane its own of them, in order.  The others add an exact zero.
+      for (int e0 = slice; e0 < n; e0 += 64 * S) {
+        uint32_t todo[2] = {0u, 0u};
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll 8
+          for (int b = 0; b < 32; ++b) {
+            const int e = e0 + (32 * w + b) * S;
+            const SrRec64 &s = src[min(e, n - 1)];
+            const float fx = (float)(int32_t)((me.x - s.x) >> 32) * fux, fy = (float)(int32_t)((me.y - s.y) >> 32) * fur,
+                        fz = (float)(int32_t)((me.z - s.z) >> 32) * fur;
+            if (e < n && fmaf(fx, fx, fmaf(fy, fy, fz * fz)) < frmax2) todo[w] |= 1u << b;
+          }
+        uint64_t list = (uint64_t)todo[1] << 32 | todo[0];
+        while (list) {
+          const SrRec64 s = src[e0 + (int)__builtin_ctzll(list) * S];
+          list &= list - 1;
+          const double dx = double((int64_t)(me.x - s.x)) * ux;
+          const double dy = double(me.y - s.y) * ur;
+          const double dz = double(me.z - s.z) * ur;
+          const double r2 = dx * dx + dy * dy + dz * dz;
+          const double dij = 0.5 * (me.d + s.d);
+          double f = 0.0;
+          if (r2 < rmax2 && r2 > 0.0) {
+            const double r = sqrt(r2);
+            const double gg = c2 * exp(-a * a * r2) / r;
+            f = (r >= dij ? erfc(a * r) / r2 + gg : 1.0 / (dij * dij) - (erf(a * r) / r2 - gg)) * s.q / r;
+          }
+          sx += f * dx;
+          sy += f * dy;
+          sz += f * dz;
         }
-        sx += f * dx;
-        sy += f * dy;
-        sz += f * dz;
       }
     }
     part[0][g] = sx;
@@ -1295,7 +1319,9 @@ template <class Real> void launch_p3m(const State<Real> &st, const Phys &ph, con
     hipLaunchKernelGGL(k_p3m_short_f32, dim3(ncell), dim3(kSrLanes), 0, s, st, ph, m, m.starts, m.sorted, rec,
                        (const float *)(rec + ph.N), m.slong, m.table);
   } else {
-    hipLaunchKernelGGL(k_p3m_short_f64, dim3(ncell), dim3(kSrLanes), 0, s, st, ph, m, m.starts, m.sorted,
+    // workgroups for twice the mean number of targets per cell (the cells in the section's corners are empty)
+    const int blocks = std::max(1, std::min(64, (2 * (ph.N / ncell) + kSrTargets - 1) / kSrTargets));
+    hipLaunchKernelGGL(k_p3m_short_f64, dim3(ncell, blocks), dim3(kSrLanes), 0, s, st, ph, m, m.starts, m.sorted,
                        (const SrRec64 *)m.rec, m.slong);
   }
 }
