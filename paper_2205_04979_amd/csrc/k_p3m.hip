@@ -223,20 +223,25 @@ __global__ __launch_bounds__(256) void k_fft_lines(double2 *__restrict__ data, i
 // ---- the step's transforms
 //
 // Charge and fields are real, so half a spectrum holds everything: kz < P/2 as [x][y][kz], xs values per x,
-// and the plane kz = P/2 behind it as [x][y].  Five passes, each reading and writing its lines once:
-//   charge   z: two real rows as one complex line, unpacked into their half spectra
-//   y        forward, the rows y >= nc taken as zero
-//   x        forward, times the three Green's functions, and each product back, without leaving LDS
-//   y        inverse of the three, only the rows y < nc stored
-//   fields   z: (E_x, E_y) of a row as one complex line, E_z of two rows as another; the three
-//            components of a node side by side for the interpolation
-// Bound by memory: at 256 x 256 x 256 (128 nodes across) 0.95 GB a step where the full complex spectra
+// and the plane kz = P/2 behind it as [x][y].  The passes, each reading and writing its lines once:
+//   charge   z: real rows, half of their spectra stored
+//   y, x     forward, the rows y >= nc taken as zero
+//   fields   z: the products with the Green's functions, E_x + i E_y as one set of lines and E_z as another,
+//            both halves of each line from the half spectrum; only the points z < nc are stored
+//   y        inverse, only the rows y < nc stored
+//   x        inverse, the lines y, z < nc; the three components of a node side by side for the interpolation
+// Order, butterflies, packing and rounding are those of a transform over the full spectra, bit for bit: the
+// upper half of each is the conjugate of the lower one in floating point too, since the twiddles are symmetric
+// to the last bit and the multiplications round alike under a change of sign.  (Shorter by a tenth with other
+// roundings -- two rows in one line, the products between the x passes -- but then a step in FP32 differs in
+// its last bits, and over 100 steps of 2^20 particles a pair that nearly collides makes 1e-2 of it.)
+// Bound by memory: at 256 x 256 x 256 (128 nodes across) 1.2 GB a step where the full complex spectra
 // moved 1.9 GB.  The y and x passes take as many lines at a time as make 128 bytes (a strided segment),
-// fewer where the lines are long; the z passes enough to fill the chip with workgroups.  Measured, a step's transforms: 256^3 568 -> 255 us, 128^3 105 -> 59 us
-// (nine passes over full spectra before).  Loads and the Green's functions of the next component are issued
-// ahead of the butterflies, none under a branch (x pass 135 -> 111 us).
+// fewer where the lines are long; the z passes enough to fill the chip with workgroups.  Measured, a step's
+// transforms: 256^3 568 -> 289 us, 128^3 105 -> 67 us (nine passes over full spectra before).  Loads are issued
+// ahead of the butterflies, none under a branch.
 constexpr int kFftMaxValues = 32768;   // bytes of line data per workgroup in the y and x passes, at most
-constexpr int kZTile = 1024;           // values per workgroup of the charge pass and per third of the fields pass
+constexpr int kZTile = 1024;           // values per workgroup of the charge pass and of the spectrum per workgroup of the fields z pass
 constexpr int kZThreads = 256;
 // values each thread of the y and x passes holds
 template <class T> constexpr int kFftPer = 64 / sizeof(T);
@@ -258,7 +263,7 @@ __device__ __forceinline__ void fft_twiddles(T *tw, const T *__restrict__ table,
 }
 
 // In-place transforms of bit-reversed lines, radix-2 stages in pairs; begins and ends with a barrier.
-template <int SIGN, class T>
+template <class T>
 __device__ __forceinline__ void fft_stages(T *buf, const T *tw, int log2n, int lines) {
   const int n = 1 << log2n, ls = fft_line(n);
   __syncthreads();
@@ -271,8 +276,8 @@ __device__ __forceinline__ void fft_stages(T *buf, const T *tw, int log2n, int l
       T *l = buf + (b >> (log2n - 2)) * ls;
       const int i0 = ((k >> (lg - 1)) << (lg + 1)) + pos;
       const int p0 = fft_at(i0), p1 = fft_at(i0 + half), p2 = fft_at(i0 + 2 * half), p3 = fft_at(i0 + 3 * half);
-      const T w1 = tw[pos << (log2n - lg)], w2 = tw[pos << (log2n - lg - 1)];
-      const T w3 = SIGN < 0 ? T{w2.y, -w2.x} : T{-w2.y, w2.x};   // a quarter turn on
+      const T w1 = tw[pos << (log2n - lg)];
+      const T w2 = tw[pos << (log2n - lg - 1)], w3 = tw[(pos + half) << (log2n - lg - 1)];
       const T a0 = l[p0], a1 = l[p1], a2 = l[p2], a3 = l[p3];
       T v = cmul(w1, a1);
       const T b0 = cadd(a0, v), b1 = csub(a0, v);
@@ -302,40 +307,27 @@ __device__ __forceinline__ void fft_stages(T *buf, const T *tw, int log2n, int l
 
 __device__ __forceinline__ int fft_rev(int p, int log2n) { return fft_at((int)(__brev((unsigned)p) >> (32 - log2n))); }
 
-// z pass of the charge: rows 2g and 2g + 1 (row = x nc + y) as the real and imaginary part of line g.
+// z pass of the charge: rows x nc + y, half of each one's spectrum stored.
 template <class T>
 __global__ __launch_bounds__(kZThreads) void k_fft_charge(P3mDev m, int log2p, T *__restrict__ spec) {
-  constexpr int TILE = kZTile;
-  __shared__ T buf[fft_lds(TILE)];
+  __shared__ T buf[fft_lds(kZTile)];
   __shared__ T tw[kTwiddles / 2];
-  const int n = 1 << log2p, ls = fft_line(n), nc = m.nc, KZ = n / 2, lines = TILE >> log2p;
-  const int64_t g0 = (int64_t)blockIdx.x * lines;
-  const double inv = 1.0 / *m.q_scale;
+  const int n = 1 << log2p, ls = fft_line(n), nc = m.nc, KZ = n / 2, lines = kZTile >> log2p;
+  const int64_t r0 = (int64_t)blockIdx.x * lines;
   fft_twiddles<-1>(tw, (const T *)m.twiddles, log2p);
-  for (int e = threadIdx.x; e < TILE; e += kZThreads) {
+  for (int e = threadIdx.x; e < kZTile; e += kZThreads) {
     const int line = e >> log2p, p = e & (n - 1);
     T v = cplx<T>(0.0, 0.0);
-    if (p < nc) {
-      const unsigned long long *q = m.qmesh + 2 * (g0 + line) * nc + p;
-      v = cplx<T>((double)(long long)q[0] * inv, (double)(long long)q[nc] * inv);
-    }
+    if (p < nc) v = cplx<T>((double)(long long)m.qmesh[(r0 + line) * nc + p] / *m.q_scale, 0.0);
     buf[line * ls + fft_rev(p, log2p)] = v;
   }
-  fft_stages<-1>(buf, tw, log2p, lines);
+  fft_stages(buf, tw, log2p, lines);
   T *nyq = spec + m.nx * m.xs;
-  for (int e = threadIdx.x; e < TILE / 2; e += kZThreads) {
+  for (int e = threadIdx.x; e < kZTile / 2; e += kZThreads) {
     const int line = e >> (log2p - 1), k = e & (KZ - 1);
-    const T *l = buf + line * ls;
-    const T c1 = l[fft_at(k)], c2 = l[fft_at((n - k) & (n - 1))];
-    const int64_t r = 2 * (g0 + line), x = r / nc, y = r % nc;   // nc is even: both rows of one x
-    T *o = spec + x * m.xs + y * KZ + k;
-    o[0] = T{(c1.x + c2.x) / 2, (c1.y - c2.y) / 2};
-    o[KZ] = T{(c1.y + c2.y) / 2, (c2.x - c1.x) / 2};
-    if (k == 0) {
-      const T c = l[fft_at(KZ)];
-      nyq[x * n + y] = T{c.x, 0};
-      nyq[x * n + y + 1] = T{c.y, 0};
-    }
+    const int64_t x = (r0 + line) / nc, y = (r0 + line) % nc;
+    spec[x * m.xs + y * KZ + k] = buf[line * ls + fft_at(k)];
+    if (k == 0) nyq[x * n + y] = buf[line * ls + fft_at(KZ)];
   }
 }
 
@@ -366,18 +358,17 @@ __global__ __launch_bounds__(512) void k_fft_y(P3mDev m, int log2p, int log2l, i
     v[r] = SIGN > 0 || r < HALF ? o[(int64_t)point_of(r) << log2d] : cplx<T>(0.0, 0.0);
 #pragma unroll
   for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2p)] = v[r];
-  fft_stages<SIGN>(buf, tw, log2p, lines);
+  fft_stages(buf, tw, log2p, lines);
   if (l0 + line_of(0) >= n_lines) return;
 #pragma unroll
   for (int r = 0; r < (SIGN < 0 ? PER : HALF); ++r)
     o[(int64_t)point_of(r) << log2d] = buf[line_of(r) * ls + fft_at(point_of(r))];
 }
 
-// x pass: lines (ky, kz), then those of the plane kz = P/2: the charge's spectrum in spec, the three
-// fields' (transformed back along x) out to spec, spec + comp_stride, spec + 2 comp_stride.
+// x pass of the charge: lines (ky, kz), then those of the plane kz = P/2.
 template <class T>
 __global__ __launch_bounds__(512) void k_fft_x(P3mDev m, int log2x, int log2p, int log2l, int main_blocks,
-                                               int64_t comp_stride, T *__restrict__ spec) {
+                                               T *__restrict__ spec) {
   constexpr int PER = kFftPer<T>;
   extern __shared__ char lds[];
   const int n = 1 << log2x, ls = fft_line(n), lines = 1 << log2l;
@@ -389,84 +380,115 @@ __global__ __launch_bounds__(512) void k_fft_x(P3mDev m, int log2x, int log2p, i
   const int64_t dist = plane ? m.P : m.xs, base = plane ? n * m.xs : 0;   // distance of a line's points
   auto line_of = [&](int r) { return (int)(threadIdx.x + r * blockDim.x) & (lines - 1); };
   auto point_of = [&](int r) { return (int)(threadIdx.x + r * blockDim.x) >> log2l; };
-  const int64_t l = min(l0 + line_of(0), n_lines - 1);   // as in the y pass
-  auto at = [&](int r) { return base + l + point_of(r) * dist; };
-  T a[PER], g[PER];   // the spectrum; a Green's function, read one component ahead
-  auto read_green = [&](int c) {
-    const T *__restrict__ gc = (const T *)m.ghat[c];
+  T *o = spec + base + min(l0 + line_of(0), n_lines - 1);   // as in the y pass
+  T v[PER];
 #pragma unroll
-    for (int r = 0; r < PER; ++r) g[r] = gc[at(r)];
-  };
+  for (int r = 0; r < PER; ++r) v[r] = o[point_of(r) * dist];
 #pragma unroll
-  for (int r = 0; r < PER; ++r) a[r] = spec[at(r)];
-  read_green(0);
+  for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2x)] = v[r];
+  fft_stages(buf, tw, log2x, lines);
+  if (l0 + line_of(0) >= n_lines) return;
 #pragma unroll
-  for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2x)] = a[r];
-  fft_stages<-1>(buf, tw, log2x, lines);
-#pragma unroll
-  for (int r = 0; r < PER; ++r) a[r] = buf[line_of(r) * ls + fft_at(point_of(r))];
-  __syncthreads();
-  for (int k = threadIdx.x; k < n / 2; k += blockDim.x) tw[k].y = -tw[k].y;
-#pragma unroll
-  for (int c = 0; c < 3; ++c) {
-#pragma unroll
-    for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2x)] = cmul(a[r], g[r]);
-    if (c < 2) read_green(c + 1);
-    fft_stages<1>(buf, tw, log2x, lines);
-    if (l0 + line_of(0) < n_lines) {
-#pragma unroll
-      for (int r = 0; r < PER; ++r) spec[c * comp_stride + at(r)] = buf[line_of(r) * ls + fft_at(point_of(r))];
-    }
-    __syncthreads();
-  }
+  for (int r = 0; r < PER; ++r) o[point_of(r) * dist] = buf[line_of(r) * ls + fft_at(point_of(r))];
 }
 
-// z pass of the fields: rows 2u and 2u + 1 make three complex lines, (E_x, E_y) of each and E_z of both.
+// x pass of the fields, the last one: lines (y < nc, z < nc) of E_x + i E_y (spec + comp_stride) and of E_z
+// (spec + 2 comp_stride) to the field components at the nodes.
 template <class T>
-__global__ __launch_bounds__(kZThreads) void k_fft_fields(P3mDev m, int log2p, int64_t comp_stride,
-                                                            const T *__restrict__ spec,
-                                                            FieldT<T> *__restrict__ field) {
-  __shared__ T buf[fft_lds(3 * kZTile)];
+__global__ __launch_bounds__(512) void k_fft_field_x(P3mDev m, int log2x, int log2l, int64_t comp_stride,
+                                                     const T *__restrict__ spec, FieldT<T> *__restrict__ field) {
+  constexpr int PER = kFftPer<T>;
+  extern __shared__ char lds[];
+  const int n = 1 << log2x, ls = fft_line(n), lines = 1 << log2l;
+  T *buf = reinterpret_cast<T *>(lds), *tw = buf + lines * ls;
+  fft_twiddles<1>(tw, (const T *)m.twiddles, log2x);
+  auto line_of = [&](int r) { return (int)(threadIdx.x + r * blockDim.x) & (lines - 1); };
+  auto point_of = [&](int r) { return (int)(threadIdx.x + r * blockDim.x) >> log2l; };
+  const int64_t l = ((int64_t)blockIdx.x << log2l) + line_of(0);   // y nc + z: z runs over P / 2 = nc values
+  T xy[PER], z[PER];
+#pragma unroll
+  for (int r = 0; r < PER; ++r) {
+    xy[r] = spec[comp_stride + l + point_of(r) * m.xs];
+    z[r] = spec[2 * comp_stride + l + point_of(r) * m.xs];
+  }
+#pragma unroll
+  for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2x)] = xy[r];
+  fft_stages(buf, tw, log2x, lines);
+#pragma unroll
+  for (int r = 0; r < PER; ++r) xy[r] = buf[line_of(r) * ls + fft_at(point_of(r))];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < PER; ++r) buf[line_of(r) * ls + fft_rev(point_of(r), log2x)] = z[r];
+  fft_stages(buf, tw, log2x, lines);
+#pragma unroll
+  for (int r = 0; r < PER; ++r)
+    field[(int64_t)point_of(r) * m.nc * m.nc + l] =
+        FieldT<T>{xy[r].x, xy[r].y, buf[line_of(r) * ls + fft_at(point_of(r))].x, 0};
+}
+
+// z pass of the fields, from the charge's half spectrum: E_x + i E_y to spec + comp_stride or E_z (EZ) to
+// spec + 2 comp_stride, the points z < nc.  The product a g at (-kx, -ky, -kz) is the conjugate of that
+// at (kx, ky, kz) (charge and Green's functions are real on the mesh), so a workgroup takes a row and its
+// mirror image (for ky = 0 the rows ky = 0 and P / 2, whose images it reads besides).
+template <class T, bool EZ>
+__global__ __launch_bounds__(kZThreads) void k_fft_field_z(P3mDev m, int log2p, int64_t comp_stride,
+                                                           T *__restrict__ spec) {
+  __shared__ T buf[fft_lds(2 * kZTile)];
   __shared__ T tw[kTwiddles / 2];
-  const int n = 1 << log2p, ls = fft_line(n), nc = m.nc, KZ = n / 2, units = kZTile >> log2p;
-  const int64_t u0 = (int64_t)blockIdx.x * units, main = m.nx * m.xs;
+  const int n = 1 << log2p, ls = fft_line(n), nx = m.nx, KZ = n / 2, units = kZTile >> log2p;
+  const int64_t u0 = (int64_t)blockIdx.x * units, main = nx * m.xs;
+  const T *__restrict__ ga = (const T *)m.ghat[EZ ? 2 : 0], *__restrict__ gb = (const T *)m.ghat[1];
   fft_twiddles<1>(tw, (const T *)m.twiddles, log2p);
-  // a and b, real along z, as a + i b: both halves of the spectrum
-  auto put = [&](T *l, int k, T a, T b) {
-    if (k == 0) {
-      l[fft_rev(0, log2p)] = T{a.x, b.x};
+  // unit u: x = u / KZ, y = u % KZ; its row j
+  auto row = [&](int64_t u, int j, int &x, int &y) {
+    x = (int)(u >> (log2p - 1));
+    y = (int)(u & (KZ - 1));
+    if (j == 0) return;
+    if (y == 0) {
+      y = KZ;
     } else {
-      l[fft_rev(k, log2p)] = T{a.x - b.y, a.y + b.x};
-      l[fft_rev(n - k, log2p)] = T{a.x + b.y, b.x - a.y};
+      x = x == 0 ? 0 : nx - x;
+      y = n - y;
     }
   };
-  for (int e = threadIdx.x; e < units << (log2p - 1); e += kZThreads) {
-    const int u = e >> (log2p - 1), k = e & (KZ - 1);
-    const int64_t r = 2 * (u0 + u), x = r / nc, y = r % nc;
-    T v[3][2];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      const T *s = spec + c * comp_stride + x * m.xs + y * KZ + k;
-      v[c][0] = s[0];
-      v[c][1] = s[KZ];
+  // a g1 + i a g2, or a g1 alone; of the conjugates where mirror is set.  The rounding is written out: left to
+  // the compiler, a product and its mirror image share a term and round differently, and the two halves of
+  // the spectrum no longer match to the last bit.
+  auto mul = [](T a, T g) {
+    return T{__builtin_elementwise_fma(a.x, g.x, -(a.y * g.y)), __builtin_elementwise_fma(a.y, g.x, a.x * g.y)};
+  };
+  auto product = [&](int64_t at, bool mirror) {
+    auto conj = [&](T v) { return mirror ? T{v.x, -v.y} : v; };
+    const T a = conj(spec[at]), pp = mul(a, conj(ga[at]));
+    if constexpr (EZ) {
+      return pp;
+    } else {
+      const T qq = mul(a, conj(gb[at]));
+      return T{pp.x - qq.y, pp.y + qq.x};
     }
-    T *l = buf + 3 * u * ls;
-    put(l, k, v[0][0], v[1][0]);
-    put(l + ls, k, v[0][1], v[1][1]);
-    put(l + 2 * ls, k, v[2][0], v[2][1]);
+  };
+  for (int e = threadIdx.x; e < units << log2p; e += kZThreads) {
+    const int k = e & (KZ - 1), j = (e >> (log2p - 1)) & 1, u = e >> log2p;
+    int x, y;
+    row(u0 + u, j, x, y);
+    const int64_t at = x * m.xs + (int64_t)y * KZ + k;
+    T *own = buf + (2 * u + j) * ls;
+    own[fft_rev(k, log2p)] = product(at, false);
     if (k == 0) {
-      const T *s = spec + main + x * n + y;
-      l[fft_rev(KZ, log2p)] = T{s[0].x, s[comp_stride].x};
-      l[ls + fft_rev(KZ, log2p)] = T{s[1].x, s[comp_stride + 1].x};
-      l[2 * ls + fft_rev(KZ, log2p)] = T{s[2 * comp_stride].x, s[2 * comp_stride + 1].x};
+      own[fft_rev(KZ, log2p)] = product(main + (int64_t)x * n + y, false);
+    } else if ((y & (KZ - 1)) == 0) {
+      own[fft_rev(n - k, log2p)] = product((x == 0 ? 0 : nx - x) * m.xs + (int64_t)y * KZ + k, true);
+    } else {
+      buf[(2 * u + 1 - j) * ls + fft_rev(n - k, log2p)] = product(at, true);
     }
   }
-  fft_stages<1>(buf, tw, log2p, 3 * units);
-  for (int e = threadIdx.x; e < units * 2 * nc; e += kZThreads) {
-    const int p = e & (nc - 1), row = e >> (log2p - 1);   // row within the workgroup; nc = n / 2
-    const T *l = buf + 3 * (row >> 1) * ls;
-    const T xy = l[(row & 1) * ls + fft_at(p)], z = l[2 * ls + fft_at(p)];
-    field[(2 * u0 + row) * nc + p] = FieldT<T>{xy.x, xy.y, row & 1 ? z.y : z.x, 0};
+  fft_stages(buf, tw, log2p, 2 * units);
+  T *out = spec + (EZ ? 2 : 1) * comp_stride;
+  for (int e = threadIdx.x; e < units << log2p; e += kZThreads) {
+    const int z = e & (KZ - 1), j = (e >> (log2p - 1)) & 1, u = e >> log2p;
+    int x, y;
+    row(u0 + u, j, x, y);
+    out[x * m.xs + (int64_t)y * KZ + z] = buf[(2 * u + j) * ls + fft_at(z)];
   }
 }
 
@@ -1217,7 +1239,6 @@ int ilog2(int n) {
 template <class T> void fft_fields(const P3mDev &m, hipStream_t s) {
   const int lp = ilog2(m.P), lx = ilog2(m.nx);
   const int64_t lines = (int64_t)m.nx * m.P / 2, stride = p3m_spectrum_values(m);   // y lines (x: P P / 2)
-  const unsigned z_blocks = (unsigned)((int64_t)m.nx * m.nc / 2 * m.P / kZTile);
   T *spec = (T *)m.spec;
   // 2^lines_of lines of 2^log2n points per workgroup; at least a wave's threads
   auto lines_of = [](int log2n) {
@@ -1232,15 +1253,18 @@ template <class T> void fft_fields(const P3mDev &m, hipStream_t s) {
   const int ly = lines_of(lp), lw = lines_of(lx);
   const int main_y = (int)(lines >> ly), plane_y = (m.nx + (1 << ly) - 1) >> ly;
   const int main_x = (int)((int64_t)m.P * m.P / 2 >> lw), plane_x = (m.P + (1 << lw) - 1) >> lw;
-  hipLaunchKernelGGL(k_fft_charge<T>, dim3(z_blocks), dim3(kZThreads), 0, s, m, lp, spec);
+  hipLaunchKernelGGL(k_fft_charge<T>, dim3((unsigned)((int64_t)m.nx * m.nc * m.P / kZTile)), dim3(kZThreads), 0, s, m,
+                     lp, spec);
   hipLaunchKernelGGL((k_fft_y<-1, T>), dim3(main_y + plane_y), threads(lp, ly), bytes(lp, ly), s, m, lp, ly, main_y,
                      stride, spec);
-  hipLaunchKernelGGL(k_fft_x<T>, dim3(main_x + plane_x), threads(lx, lw), bytes(lx, lw), s, m, lx, lp, lw, main_x,
-                     stride, spec);
-  hipLaunchKernelGGL((k_fft_y<1, T>), dim3(main_y + plane_y, 3), threads(lp, ly), bytes(lp, ly), s, m, lp, ly, main_y,
-                     stride, spec);
-  hipLaunchKernelGGL(k_fft_fields<T>, dim3(z_blocks), dim3(kZThreads), 0, s, m, lp, stride, spec,
-                     (FieldT<T> *)m.field);
+  hipLaunchKernelGGL(k_fft_x<T>, dim3(main_x + plane_x), threads(lx, lw), bytes(lx, lw), s, m, lx, lp, lw, main_x, spec);
+  const dim3 field_z((unsigned)((int64_t)m.nx * m.P / 2 * m.P / kZTile));
+  hipLaunchKernelGGL((k_fft_field_z<T, false>), field_z, dim3(kZThreads), 0, s, m, lp, stride, spec);
+  hipLaunchKernelGGL((k_fft_field_z<T, true>), field_z, dim3(kZThreads), 0, s, m, lp, stride, spec);
+  hipLaunchKernelGGL((k_fft_y<1, T>), dim3(main_y, 2), threads(lp, ly), bytes(lp, ly), s, m, lp, ly, main_y, stride,
+                     spec + stride);
+  hipLaunchKernelGGL(k_fft_field_x<T>, dim3((unsigned)((int64_t)m.nc * m.nc >> lw)), threads(lx, lw), bytes(lx, lw), s, m,
+                     lx, lw, stride, spec, (FieldT<T> *)m.field);
 }
 
 // Forward transform of a whole FP64 mesh (set-up): lines along z, y, x.
