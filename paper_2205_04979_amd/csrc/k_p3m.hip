@@ -1310,7 +1310,9 @@ int64_t p3m_spectrum_values(const P3mDev &m) { return m.nx * (m.xs + m.P); }
 
 size_t p3m_mesh_bytes(const P3mDev &m, size_t real_bytes) {
   const size_t run = 2 * real_bytes * 3 * p3m_spectrum_values(m) + 4 * real_bytes * m.nx * m.nc * m.nc;
-  return std::max(run, sizeof(double2) * m.nx * m.P * m.P);
+  // with the three Green's functions not less than five full meshes, which is what a workspace is sized for
+  const size_t full = 2 * real_bytes * m.nx * m.P * m.P, green = 2 * real_bytes * 3 * p3m_spectrum_values(m);
+  return std::max({run, sizeof(double2) * m.nx * m.P * m.P, 5 * full > green ? 5 * full - green : 0});
 }
 
 void p3m_setup_green(const P3mDev &m, double L, int images, bool fp32_mesh, hipStream_t s) {

@@ -84,11 +84,11 @@ struct P3mDev {
 };
 int64_t p3m_plane_values(const P3mDev &m, size_t real_bytes);   // xs
 int64_t p3m_spectrum_values(const P3mDev &m);                  // complex values of a half spectrum
-size_t p3m_mesh_bytes(const P3mDev &m, size_t real_bytes);     // spec and field, at least one full FP64 mesh
+size_t p3m_mesh_bytes(const P3mDev &m, size_t real_bytes);     // spec and field (a full FP64 mesh fits)
 void p3m_setup_green(const P3mDev &m, double L, int images, bool fp32_mesh, hipStream_t s);
 template <class Real> void launch_p3m(const State<Real> &st, const Phys &ph, const P3mDev &m, hipStream_t s);
 
-// One-dimensional Eulerian low-fidelity model, one lane per particle class.
+// One-dimensional Eulerian low-fidelity model.
 struct LfConst {
   double R, nu, rho_f, rho_p, re_tau, eps0;
   int n_wall, n_core;
