@@ -434,7 +434,7 @@ def lf_run() -> dict:
     ms = ev0.elapsed_time(ev1) / reps
     res = {"classes": n, "nodes": 1600, "ms_per_launch": round(ms, 4), "classes_per_s": round(n / (ms * 1e-3), 1),
            "vdep_plus_median": float(np.median(out.cpu().numpy())),
-           "note": "one lane per class, single inward pass (momentum march with the flux carried as an affine map)"}
+           "note": "node work spread over a workgroup's waves, single inward pass (momentum march with the flux carried as an affine map)"}
     log(f"[bench] lf: {res}")
     return res
 
