@@ -113,9 +113,10 @@ __device__ __forceinline__ double rms_fluid_plus(double y) {
   return quot(0.005 * y2, fma(0.002923 * y2, fma(two_k, p, two_k), 1.0));
 }
 
-// Positive root V of V^2 / 2 + a V = w (a > 0), 0 for w <= 0.  The hardware's FP32 reciprocal root
+// Positive root V of V^2 / 2 + a V = w, 0 for w <= 0.  The hardware's FP32 reciprocal root
 // and reciprocal give V and the slope's inverse 1 / (V + a) = 1 / sqrt(a^2 + 2 w) to about 2^-21; two
 // Newton steps in FP64 take V to its last digit: a shorter chain than an FP64 root and quotient.
+// For a >= 0: sqrt(a^2 + 2 w) + a cancels otherwise, and FP32 may keep no digit of it.
 // far: set where FP32's range does not hold the operands (the caller then takes speed_far).
 __device__ __forceinline__ double speed(double a, double w, bool &far) {
   w = fmax(w, 0.0);
@@ -276,6 +277,9 @@ k_lf(LfConst c, int64_t n, const double *__restrict__ d_diam, const double *__re
   // the chain wave: issues ahead of the node waves that share its SIMD
   __builtin_amdgcn_s_setprio(3);
   const bool lane = id < C;
+  // A pipe of less than a wall unit beyond the particle makes the core's cells run backwards (a < 0), a wall
+  // unit below the smallest gap the wall's: such a class takes speed_far throughout.
+  const bool back = !(c.R / lw - yw > 1.001) || !(kGapMin < lw);
   double V = 0.0, Vwall = 0.0;   // speed toward the wall at the last node; at the wall
   double s = 1.0, b = 0.0;       // flux coefficients at the last node
   __syncthreads();
@@ -301,7 +305,7 @@ k_lf(LfConst c, int64_t n, const double *__restrict__ d_diam, const double *__re
       }
       for (int k0 = 0; k0 < NC; k0 += NB) {
         const int kn = k0 + NB < NC ? k0 + NB : 0;
-        bool far = false;
+        bool far = back;
         const double K0 = 0.5 * V * V;
         double K = K0;
 #pragma unroll

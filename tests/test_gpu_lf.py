@@ -151,3 +151,27 @@ def test_lf_batch_size_does_not_change_a_class(n):
     small = np.concatenate([lf_solve(p, d[k], q[k], A[k], n_wall=40, n_core=30) for k in np.array_split(pick, 4) if k.size])
     assert np.array_equal(np.isnan(g), bad)
     assert np.array_equal(g[pick], small, equal_nan=True)
+
+
+@pytest.mark.parametrize("re_tau,d_range,a_decades", [(0.3, (1e-9, 1e-4), (-26, -18)), (0.9, (1e-8, 1e-3), (-22, -12)),
+                                                      (0.5, (1e-7, 1e-3), (-22, -12)), (180.0, (4e-3, 0.05), (-16, -8))])
+def test_lf_cells_that_run_backwards_against_oracle(re_tau, d_range, a_decades):
+    """A pipe radius of less than one wall unit beyond the particle (Re_tau below 1, or a particle as large as
+    the pipe) makes the core's spacing negative; such classes, repulsive cohesion (A < 0) among them, are
+    accepted and give the oracle's value.  The root of a backward cell cancels in both evaluations, so classes
+    that a change of d by 1e-13 moves by 1e-10 are left out, and the others agree to ten times that."""
+    from paper_2205_04979_amd.depo import lf_solve
+    rng = np.random.default_rng(11)
+    p = physical_params(re_tau)
+    n = 60
+    d = np.exp(rng.uniform(np.log(d_range[0]), np.log(d_range[1]), n))
+    q = np.where(np.arange(n) % 3 == 0, 0.0, rng.normal(size=n) * 10.0 ** rng.uniform(-24, -18, n))
+    A = rng.normal(size=n) * 10.0 ** rng.uniform(*a_decades, n)
+    assert ((1 - 0.5 * d / p["R"]) * re_tau < 1).any()
+    say("case: LF backwards", re_tau)
+    with np.errstate(all="ignore"):
+        o, o2 = (np.array([olf.solve(p, *r, n_wall=200, n_core=100) for r in zip(k * d, q, A)]) for k in (1.0, 1.0 + 1e-13))
+        keep = np.isfinite(o) & (np.abs(o2 / o - 1) < 1e-10)
+    assert keep.sum() > 50
+    g = lf_solve(p, d, q, A, n_wall=200, n_core=100)
+    assert np.allclose(g[keep], o[keep], rtol=1e-9, atol=0), np.max(np.abs(g[keep] / o[keep] - 1))
