@@ -564,20 +564,19 @@ template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGra
 
 template <class Real> depo_status run_steps(depo_ctx *ctx, int n, hipStream_t s) {
   if (n == 0) return DEPO_OK;
-  if (ctx->use_graph) {
-    int k = 0;
-    if (n >= kBatchFrom) {
-      if (!ctx->gexec_batch)
-        if (depo_status e = capture_steps<Real>(ctx, kBatch, ctx->gexec_batch); e != DEPO_OK) return e;
-      for (; k + kBatch <= n; k += kBatch) HIP_TRY(hipGraphLaunch(ctx->gexec_batch, s));
-    }
-    if (k < n && !ctx->gexec)
-      if (depo_status e = capture_steps<Real>(ctx, 1, ctx->gexec); e != DEPO_OK) return e;
-    for (; k < n; ++k) HIP_TRY(hipGraphLaunch(ctx->gexec, s));
-  } else {
-    for (int k = 0; k < n; ++k) HIP_TRY(enqueue_steps<Real>(ctx, s, s, 1));
+  if (!ctx->use_graph) {
+    for (int k = 0; k < n; ++k, ++ctx->nstep) HIP_TRY(enqueue_steps<Real>(ctx, s, s, 1));
+    return DEPO_OK;
   }
-  ctx->nstep += n;
+  // what the call needs is captured before its first launch: one that cannot be captured leaves the state
+  // and the step counters as they were
+  const int batches = n >= kBatchFrom ? n / kBatch : 0, singles = n - batches * kBatch;
+  if (batches && !ctx->gexec_batch)
+    if (depo_status e = capture_steps<Real>(ctx, kBatch, ctx->gexec_batch); e != DEPO_OK) return e;
+  if (singles && !ctx->gexec)
+    if (depo_status e = capture_steps<Real>(ctx, 1, ctx->gexec); e != DEPO_OK) return e;
+  for (int k = 0; k < batches; ++k, ctx->nstep += kBatch) HIP_TRY(hipGraphLaunch(ctx->gexec_batch, s));
+  for (int k = 0; k < singles; ++k, ++ctx->nstep) HIP_TRY(hipGraphLaunch(ctx->gexec, s));
   return DEPO_OK;
 }
 
