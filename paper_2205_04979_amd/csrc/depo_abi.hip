@@ -26,8 +26,11 @@ constexpr int kSimds = 1024;           // 256 CUs x 4
 constexpr int kForkBlocks = 2000;      // a step of more 64 x 64 blocks of pairs runs its forces on two branches
 // Steps per captured graph, used by calls of kBatchFrom steps and more.  It saves the gap between graphs and,
 // without a storage reorder, a launch per step (1,024 particles in FP64: 37 us a step alone, 29.7 in fours,
-// 28.8 in eights) and costs its capture (40 us more than one step's for four, 65 for eight).
-constexpr int kBatch = 4, kBatchFrom = 16;
+// 28.8 in eights) and costs its capture (40 us more than one step's for four, 65 for eight).  Where a one-step
+// graph is there already, kBatchLead steps are replayed before the capture, whose 60 to 250 us they hide (step(5), then
+// step(20), the second call with the capture first, behind eight steps, and with one-step graphs alone, us: 6,000
+// particles 965, 914, 957; 16,000 1,894, 1,840, 1,890; P3M with 65,536 5,720, 5,547, 5,626).
+constexpr int kBatch = 4, kBatchFrom = 16, kBatchLead = 8;
 // FP32 defaults: the symmetric kernel (default_sym), or the one-sided kernel where the layout has too
 // many items
 const CoulombConfig kDefaultOneSided{1, 8, 32, true};
@@ -536,10 +539,14 @@ template <class Real> hipError_t enqueue_steps(depo_ctx *ctx, hipStream_t a, hip
 // (the P3M pipeline has cell passes of its own: one branch).  Steps in FP32 with one and with two branches, us:
 // 1,024 particles 28.6, 30.9; 3,001 33.9, 34.2; 4,000 (2,016 blocks of pairs) 38.0, 36.6; 5,600 42.7, 39.6;
 // 16,000 106, 97; in FP64 the same way.
+bool forks(const depo_ctx *ctx) {
+  return short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
+         count_items(ctx->off, 64, 1) > kForkBlocks;
+}
+
 template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGraphExec_t &exec) {
   if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
-  const bool fork = short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
-                    count_items(ctx->off, 64, 1) > kForkBlocks;
+  const bool fork = forks(ctx);
   if (fork && !ctx->cap_side) {
     HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_side, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&ctx->ev_fork, hipEventDisableTiming));
@@ -562,22 +569,45 @@ template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGra
   return DEPO_OK;
 }
 
+// Whether long calls take the batch graph.  With two branches and a storage reorder between the steps, whose halves
+// then stay apart, it saves the gaps between graphs only, which a larger layout hides (128 steps in fours and
+// one by one, us: 4,500 particles 7,288 and 7,468; 9,000 8,634 and 8,767; 16,000 14,618 and 14,373; 30,000
+// 29,876 and 29,707).
+bool batch_pays(const depo_ctx *ctx) {
+  return !(forks(ctx) && reorders(ctx) && count_items(ctx->off, 64, 1) > 20000);
+}
+
 template <class Real> depo_status run_steps(depo_ctx *ctx, int n, hipStream_t s) {
   if (n == 0) return DEPO_OK;
-  if (!ctx->use_graph) {
-    for (int k = 0; k < n; ++k, ++ctx->nstep) HIP_TRY(enqueue_steps<Real>(ctx, s, s, 1));
+  auto replay = [&](hipGraphExec_t x, int steps, int times) -> depo_status {
+    for (int k = 0; k < times; ++k, ctx->nstep += steps) HIP_TRY(hipGraphLaunch(x, s));
     return DEPO_OK;
+  };
+  auto direct = [&](int steps) -> depo_status {
+    for (int k = 0; k < steps; ++k, ++ctx->nstep) HIP_TRY(enqueue_steps<Real>(ctx, s, s, 1));
+    return DEPO_OK;
+  };
+  if (!ctx->use_graph) return direct(n);
+  auto capture = [&](int steps, hipGraphExec_t &x) -> depo_status {
+    const depo_status e = capture_steps<Real>(ctx, steps, x);
+    if (e != DEPO_OK) (void)hipGetLastError();   // not the next call's
+    return e;
+  };
+  const int end = ctx->nstep + n;
+  const bool batches = n >= kBatchFrom && batch_pays(ctx);
+  // The first graph of a call is captured before its first launch: a call that cannot capture it leaves the state
+  // and the step counters as they were.  A second one it can do without.
+  if (!ctx->gexec && !ctx->gexec_batch) {
+    if (depo_status e = batches ? capture(kBatch, ctx->gexec_batch) : capture(1, ctx->gexec); e != DEPO_OK) return e;
   }
-  // what the call needs is captured before its first launch: one that cannot be captured leaves the state
-  // and the step counters as they were
-  const int batches = n >= kBatchFrom ? n / kBatch : 0, singles = n - batches * kBatch;
-  if (batches && !ctx->gexec_batch)
-    if (depo_status e = capture_steps<Real>(ctx, kBatch, ctx->gexec_batch); e != DEPO_OK) return e;
-  if (singles && !ctx->gexec)
-    if (depo_status e = capture_steps<Real>(ctx, 1, ctx->gexec); e != DEPO_OK) return e;
-  for (int k = 0; k < batches; ++k, ctx->nstep += kBatch) HIP_TRY(hipGraphLaunch(ctx->gexec_batch, s));
-  for (int k = 0; k < singles; ++k, ++ctx->nstep) HIP_TRY(hipGraphLaunch(ctx->gexec, s));
-  return DEPO_OK;
+  if (batches && !ctx->gexec_batch) {
+    if (depo_status e = replay(ctx->gexec, 1, kBatchLead); e != DEPO_OK) return e;
+    capture(kBatch, ctx->gexec_batch);
+  }
+  if (batches && ctx->gexec_batch)
+    if (depo_status e = replay(ctx->gexec_batch, kBatch, (end - ctx->nstep) / kBatch); e != DEPO_OK) return e;
+  if (ctx->nstep < end && !ctx->gexec) capture(1, ctx->gexec);
+  return ctx->gexec ? replay(ctx->gexec, 1, end - ctx->nstep) : direct(end - ctx->nstep);
 }
 
 template <class Real> depo_status run_steps_timed(depo_ctx *ctx, int n, hipStream_t s, double *ms) {

@@ -25,10 +25,12 @@ static dim3 g_, b_; static size_t sh_; static void *st_;
 /* kernels of the capture under way, of each graph, and of everything that ran */
 typedef struct { int n; int k[MAXK]; } graph;
 static graph *capturing;
-static int *ran, n_ran, captures, instantiated, replays, fail_at = -1, events;
+static int *ran, n_ran, captures, instantiated, replays, fail_at = -1, events, ran_before[64];
 int fake_captures(void) { return captures; }
 int fake_replays(void) { return replays; }
 int fake_ran(void) { return n_ran; }
+/* kernels that had run when the k-th capture since the reset began */
+int fake_ran_before_capture(int k) { return ran_before[k & 63]; }
 const char *fake_name(int i) { return name[ran[i]]; }
 void fake_reset(void) { n_ran = captures = replays = 0; fail_at = -1; }
 /* the k-th capture from now on (0: the next) fails */
@@ -54,7 +56,8 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **a, size_t sh, void *st
   for (int k = 0; k < n_fn; ++k) if (fn[k] == f) { log_kernel(k); return OK; }
   return 98;
 }
-int hipGetLastError(void) { return OK; }
+static int last;
+int hipGetLastError(void) { int e = last; last = OK; return e; }
 const char *hipGetErrorString(int e) { return e ? "failed on request" : "no error"; }
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; *p = aligned_alloc(256, (size_t)64 << 20); return OK; }
@@ -71,7 +74,8 @@ int hipEventRecord(void *e, void *s) { (void)e; (void)s; return OK; }
 int hipEventElapsedTime(float *ms, void *a, void *b) { (void)a; (void)b; *ms = 1.0f; return OK; }
 int hipStreamBeginCapture(void *s, int mode) {
   (void)s; (void)mode;
-  if (captures++ == fail_at) return 1;
+  ran_before[captures & 63] = n_ran;
+  if (captures++ == fail_at) return last = 1;
   capturing = calloc(1, sizeof(graph));
   return OK;
 }
