@@ -450,6 +450,27 @@ depo_status upload_fx_scale(depo_ctx *ctx, hipStream_t stream) {
 
 bool short_range_on(const depo_ctx *ctx) { return (ctx->p.flags & (DEPO_COLLIDE | DEPO_VDW)) != 0; }
 
+// Whether a captured step has two branches: they pay where the pair sums take far longer than their join and fork
+// (the P3M pipeline has cell passes of its own: one branch).  Steps in FP32 with one and with two branches, us:
+// 1,024 particles 28.6, 30.9; 3,001 33.9, 34.2; 4,000 (2,016 blocks of pairs) 38.0, 36.6; 5,600 42.7, 39.6;
+// 16,000 106, 97; in FP64 the same way.
+bool forks(const depo_ctx *ctx) {
+  return short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
+         count_items(ctx->off, 64, 1) > kForkBlocks;
+}
+
+// One kernel for the cell list where its workgroups, which each read every particle's cell, cost less than the
+// launches of the general build: 3,001 particles 7.8 us against 18.7; 65,536 18.2 and 22.8; 200,000 34.8
+// and 29.8, where the histogram that k_prepare then saves still makes up for it; 2^20 310 and 78.  Not beside the
+// one-sided FP32 kernels, whose few long workgroups can fill the chip exactly once: those that find the list's large
+// workgroups in their place start when the first end (a step of 65,536 particles at (1, 8) 1,708 us against 1,398;
+// of 131,072 at (2, 4) 7,631 against 6,270).  Workgroups of sixteen waves do not mind (65,536 at (1, 16) 1,339, and 1,366
+// with the general build).
+void set_cell_build(depo_ctx *ctx) {
+  const bool one_sided = !ctx->fp64() && !ctx->ccfg.symmetric && ctx->ccfg.waves < 16;
+  ctx->ph.cells_fused = ctx->N <= (1 << 17) && !(one_sided && forks(ctx)) ? 1 : 0;
+}
+
 // Returns the k_finish mode bit that the pair sums need: with defer_finish, the symmetric pair
 // kernel leaves its fixed-point accumulators to k_finish (F_PAIR_SUMS), one pass fewer per step.
 template <class Real> int enqueue_coulomb(depo_ctx *ctx, hipStream_t s, bool defer_finish = false) {
@@ -535,15 +556,7 @@ template <class Real> hipError_t enqueue_steps(depo_ctx *ctx, hipStream_t a, hip
   return hipGetLastError();
 }
 
-// Captures `steps` steps.  Two branches pay where the pair sums take far longer than their join and fork
-// (the P3M pipeline has cell passes of its own: one branch).  Steps in FP32 with one and with two branches, us:
-// 1,024 particles 28.6, 30.9; 3,001 33.9, 34.2; 4,000 (2,016 blocks of pairs) 38.0, 36.6; 5,600 42.7, 39.6;
-// 16,000 106, 97; in FP64 the same way.
-bool forks(const depo_ctx *ctx) {
-  return short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
-         count_items(ctx->off, 64, 1) > kForkBlocks;
-}
-
+// Captures `steps` steps, on two branches where they pay.
 template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGraphExec_t &exec) {
   if (!ctx->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&ctx->cap_stream, hipStreamNonBlocking));
   const bool fork = forks(ctx);
@@ -698,10 +711,7 @@ depo_status build_samples(depo_ctx *ctx, const depo_sample_params *sp, const dou
   }
   if (cells > ctx->cell_cap) return ctx->fail(DEPO_E_CAPACITY, "cell grid exceeds reserved capacity");
   ctx->n_cells = (int)cells;
-  // One kernel for the cell list where its workgroups, which each read every particle's cell, cost less than the
-  // launches of the general build: 3,001 particles 7.8 us against 18.7; 65,536 18.2 and 22.8; 200,000 34.8
-  // and 29.8, where the histogram that k_prepare then saves still makes up for it; 2^20 310 and 78.
-  ctx->ph.cells_fused = ctx->N <= (1 << 17) ? 1 : 0;
+  set_cell_build(ctx);
   ctx->dmax_all = dmax_all;
   const double dq = dmax_all * ctx->ph.inv_ux;
   ctx->ph.near2 = dq * dq;
@@ -1503,6 +1513,7 @@ depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int3
     ctx->p3m_use = true;
     ctx->use_graph = use_graph != 0;
     ctx->drop_graph();
+    set_cell_build(ctx);
     return DEPO_OK;
   }
   if (mode < DEPO_PAIR_PLAIN || mode > DEPO_PAIR_SYMMETRIC_INT || mode == DEPO_PAIR_P3M)
@@ -1529,6 +1540,7 @@ depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int3
   ctx->use_graph = use_graph != 0;
   ctx->drop_graph();
   set_record_format(ctx);
+  set_cell_build(ctx);
   if (ctx->seeded) {
     std::vector<TileDev> tiles;
     build_tiles(ctx, tiles);

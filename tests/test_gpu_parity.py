@@ -985,3 +985,27 @@ def test_batched_steps_equal_single_ones(real_bytes, n, reorder):
     for k in ("x", "v", "a", "dep_step", "neighbours"):
         assert np.array_equal(out[0][0][k], out[1][0][k]), k
     assert out[0][1] == out[1][1]
+
+
+def test_a_new_pair_shape_between_steps_keeps_the_cell_list():
+    """Shapes with their own build of the cell list (the one-sided kernels where the step has two branches) taken
+    in turn between steps: the neighbour counts and the short-range forces are those of one build throughout."""
+    w = make_workload("single-65k", n=9000, field_n=32, coulomb=True)
+    f = w.field()
+    p = dict(w.params, wall_image=False, wall_vdw=False)
+    x, q = w.x.copy(), np.zeros(w.n_particles)          # no charge: the pair kernels run and add nothing
+    for k in range(0, 4000, 2):
+        x[k + 1] = x[k] + [0.9 * 0.5 * (w.d[k] + w.d[k + 1]), 0.0, 0.0]
+    x[:, 0] = np.mod(x[:, 0], p["L"])
+    say("case: shapes in turn between steps")
+    out = []
+    for shapes in ([(4, 1, 64, 2)] * 6, [(4, 1, 64, 2), (1, 8, 32, 1), (1, 8, 32, 1), (2, 2, 64, 2), (2, 4, 32, 1), (4, 2, 64, 2)]):
+        sim, _ = seeded_pair(p, f, x, w.d, q, w.offsets, w.sample_params, 4, oracle=False)
+        for c in shapes:
+            sim.set_kernel_config(*c)
+            sim.step(3)
+        sim.eval_accel()
+        out.append(sim.read())
+    assert out[0]["neighbours"].any()          # contacts push each other apart meanwhile
+    for k in ("x", "v", "a", "neighbours", "dep_step"):
+        assert np.array_equal(out[0][k], out[1][k]), k

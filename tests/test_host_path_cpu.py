@@ -71,3 +71,29 @@ print(json.dumps([a, calls(17, 17, 3, 20)]))
 """)
     assert got[0] == [[0]] + ([[8]] if batches else [[]]) + [[]] * 3, got
     assert got[1] == ([[0, 16]] if batches else [[0]]) + [[]] * 3, got
+
+
+@pytest.mark.parametrize("real_bytes,sizes,cfg,fused", [
+    (4, [9000], (1, 8, 32, 1), False), (4, [9000], (1, 16, 32, 1), True), (4, [9000], (2, 4, 32, 1), False), (4, [3000], (1, 8, 32, 1), True),
+    (4, [9000], (4, 1, 64, 2), True), (4, [9000], (1, 4, 64, 4), True), (8, [9000], (1, 4, 16, 0), True),
+    (4, [140000], (4, 1, 64, 2), False)])
+def test_the_cell_list_of_a_step_is_built_beside_the_pair_kernel_that_runs(tmp_path, real_bytes, sizes, cfg, fused):
+    """The one-kernel cell list, whose workgroups take a CU each, stays away from the one-sided FP32 kernels where
+    both run at once; a new shape brings its own build, and the histogram goes with the build that reads it."""
+    got = run(tmp_path, f"""
+s = simulation({sizes}, {real_bytes}, cfg={cfg})
+def builds():
+    fake.fake_reset()
+    assert s.step(17) == 0
+    names = ran()
+    return [sum("k_cells_fused" in k for k in names), sum("k_cell_sort" in k for k in names)]
+out = [builds()]
+if {real_bytes} == 4 and {sizes}[0] == 9000:
+    for c in ((1, 8, 32, 1), (4, 2, 64, 2), {cfg}):
+        s.check(s._L.depo_set_kernel_config(s._h, *c, 1), "shape")
+        out.append(builds())
+print(json.dumps(out))
+""")
+    want = [17, 0] if fused else [0, 17]
+    assert got[0] == want, got
+    assert len(got) == 1 or got[1:] == [[0, 17], [17, 0], want], got
