@@ -75,7 +75,9 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb(const TileDev *__restric
 
   const int nw = SPLIT ? WAVES * parts : WAVES;   // waves that share the sources
   const int per = ((t.jcount + nw - 1) / nw + BLK - 1) / BLK * BLK;
-  const int jb = t.j0 + min(t.jcount, (piece * WAVES + w) * per);
+  // without pieces no limit is needed (je ends the loops), and an instruction more here moves the loops off their
+  // alignment (65,536 particles at (2, 8), one-sided FP32: 1,553 us, and 1,606 with it)
+  const int jb = t.j0 + (SPLIT ? min(t.jcount, (piece * WAVES + w) * per) : w * per);
   const int je = min(t.j0 + t.jcount, jb + per);
 
   Real hx[IPL], hy[IPL], hz[IPL], cx[IPL], cy[IPL], cz[IPL];
