@@ -459,18 +459,6 @@ bool forks(const depo_ctx *ctx) {
          count_items(ctx->off, 64, 1) > kForkBlocks;
 }
 
-// One kernel for the cell list where its workgroups, which each read every particle's cell, cost less than the
-// launches of the general build: 3,001 particles 7.8 us against 18.7; 65,536 18.2 and 22.8; 200,000 34.8
-// and 29.8, where the histogram that k_prepare then saves still makes up for it; 2^20 310 and 78.  Not beside the
-// one-sided FP32 kernels, whose few long workgroups can fill the chip exactly once: those that find the list's large
-// workgroups in their place start when the first end (a step of 65,536 particles at (1, 8) 1,708 us against 1,398;
-// of 131,072 at (2, 4) 7,631 against 6,270).  Workgroups of sixteen waves do not mind (65,536 at (1, 16) 1,339, and 1,366
-// with the general build).
-void set_cell_build(depo_ctx *ctx) {
-  const bool one_sided = !ctx->fp64() && !ctx->ccfg.symmetric && ctx->ccfg.waves < 16;
-  ctx->ph.cells_fused = ctx->N <= (1 << 17) && !(one_sided && forks(ctx)) ? 1 : 0;
-}
-
 // Returns the k_finish mode bit that the pair sums need: with defer_finish, the symmetric pair
 // kernel leaves its fixed-point accumulators to k_finish (F_PAIR_SUMS), one pass fewer per step.
 template <class Real> int enqueue_coulomb(depo_ctx *ctx, hipStream_t s, bool defer_finish = false) {
@@ -516,21 +504,22 @@ template <class Real> void enqueue_order(depo_ctx *ctx, hipStream_t s, int ahead
 // The forces of a step: the direct Coulomb sums and, on stream b if it is another one, the cell build and
 // the short-range forces (which touch disjoint buffers), so that the O(N) branch fills the pair kernel's
 // tail.  Returns the k_finish mode bit of the pair sums in pair_mode.
-template <class Real> hipError_t enqueue_step_forces(depo_ctx *ctx, hipStream_t a, hipStream_t b, int &pair_mode) {
+template <class Real>
+hipError_t enqueue_step_forces(depo_ctx *ctx, const Phys &ph, hipStream_t a, hipStream_t b, int &pair_mode) {
   const State<Real> &st = state<Real>(ctx);
   hipError_t e = hipSuccess;
   if (b != a) {
     if ((e = hipEventRecord(ctx->ev_fork, a)) != hipSuccess) return e;
     if ((e = hipStreamWaitEvent(b, ctx->ev_fork, 0)) != hipSuccess) return e;
   }
-  if (short_range_on(ctx)) launch_cells<Real>(st, ctx->ph, ctx->n_cells, (ctx->n_cells + 1023) / 1024, b);
+  if (short_range_on(ctx)) launch_cells<Real>(st, ph, ctx->n_cells, (ctx->n_cells + 1023) / 1024, b);
   if (b != a) {
-    launch_short_range<Real>(st, ctx->ph, ctx->n_cells, b);
+    launch_short_range<Real>(st, ph, ctx->n_cells, b);
     if ((e = hipEventRecord(ctx->ev_join, b)) != hipSuccess) return e;
   }
   pair_mode = enqueue_coulomb<Real>(ctx, a, true);
   if (b != a) return hipStreamWaitEvent(a, ctx->ev_join, 0);
-  if (short_range_on(ctx)) launch_short_range<Real>(st, ctx->ph, ctx->n_cells, a);
+  if (short_range_on(ctx)) launch_short_range<Real>(st, ph, ctx->n_cells, a);
   return hipSuccess;
 }
 
@@ -540,18 +529,24 @@ template <class Real> hipError_t enqueue_steps(depo_ctx *ctx, hipStream_t a, hip
   const State<Real> &st = state<Real>(ctx);
   const int prepare = prepare_mode(ctx) | P_KICK_DRIFT;
   const bool fuse = !reorders(ctx);
+  // Beside the one-sided FP32 kernels, whose few long workgroups can fill the chip exactly once, the cell list is not
+  // built by one kernel: those workgroups that found its large ones in their place started when the first ended
+  // (a step of 65,536 particles at (1, 8) 1,708 us against 1,398; of 131,072 at (2, 4) 7,631 against 6,270).
+  // Workgroups of sixteen waves do not mind (65,536 at (1, 16) 1,339, and 1,366 with the general build).
+  Phys ph = ctx->ph;
+  if (b != a && !ctx->fp64() && !ctx->ccfg.symmetric && ctx->ccfg.waves < 16) ph.cells_fused = 0;
   for (int k = 0; k < steps; ++k) {
     if (k == 0 || !fuse) {
       enqueue_order<Real>(ctx, a, k);
-      launch_prepare<Real>(st, ctx->ph, prepare, a, k);
+      launch_prepare<Real>(st, ph, prepare, a, k);
     }
     int pair_mode = 0;
-    if (hipError_t e = enqueue_step_forces<Real>(ctx, a, b, pair_mode); e != hipSuccess) return e;
+    if (hipError_t e = enqueue_step_forces<Real>(ctx, ph, a, b, pair_mode); e != hipSuccess) return e;
     const bool last = k + 1 == steps;
     if (!last && fuse)
-      launch_finish_prepare<Real>(st, ctx->ph, F_KICK | pair_mode, prepare, k + 1, a);
+      launch_finish_prepare<Real>(st, ph, F_KICK | pair_mode, prepare, k + 1, a);
     else
-      launch_finish<Real>(st, ctx->ph, F_KICK | pair_mode, a, last ? steps : 0);
+      launch_finish<Real>(st, ph, F_KICK | pair_mode, a, last ? steps : 0);
   }
   return hipGetLastError();
 }
@@ -711,7 +706,10 @@ depo_status build_samples(depo_ctx *ctx, const depo_sample_params *sp, const dou
   }
   if (cells > ctx->cell_cap) return ctx->fail(DEPO_E_CAPACITY, "cell grid exceeds reserved capacity");
   ctx->n_cells = (int)cells;
-  set_cell_build(ctx);
+  // One kernel for the cell list where its workgroups, which each read every particle's cell, cost less than the
+  // launches of the general build: 3,001 particles 7.8 us against 18.7; 65,536 18.2 and 22.8; 200,000 34.8
+  // and 29.8, where the histogram that k_prepare then saves still makes up for it; 2^20 310 and 78.
+  ctx->ph.cells_fused = ctx->N <= (1 << 17) ? 1 : 0;
   ctx->dmax_all = dmax_all;
   const double dq = dmax_all * ctx->ph.inv_ux;
   ctx->ph.near2 = dq * dq;
@@ -1513,7 +1511,6 @@ depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int3
     ctx->p3m_use = true;
     ctx->use_graph = use_graph != 0;
     ctx->drop_graph();
-    set_cell_build(ctx);
     return DEPO_OK;
   }
   if (mode < DEPO_PAIR_PLAIN || mode > DEPO_PAIR_SYMMETRIC_INT || mode == DEPO_PAIR_P3M)
@@ -1540,7 +1537,6 @@ depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int3
   ctx->use_graph = use_graph != 0;
   ctx->drop_graph();
   set_record_format(ctx);
-  set_cell_build(ctx);
   if (ctx->seeded) {
     std::vector<TileDev> tiles;
     build_tiles(ctx, tiles);
