@@ -295,7 +295,7 @@ __device__ __forceinline__ double rsqa(double x) {
 // waves there are, hence the pieces: four
 // samples of 6,000 to 8,000 particles 682 -> 439 us per reverse step, of 2,000 to 3,000 278 -> 209 us (with
 // the reciprocal root by one correction instead of a root and a division).
-template <class Real, int WAVES, int BLK, bool SPLIT>
+template <class Real, int WAVES, int BLK, bool SPLIT, bool UNROLL>
 __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__restrict__ tiles,
                                                             const JAdj<Real> *__restrict__ rec,
                                                             const Real *__restrict__ jr, Real *__restrict__ ox,
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__res
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nw = SPLIT ? WAVES * parts : WAVES;   // waves that share the sources
   const int per = ((t.jcount + nw - 1) / nw + BLK - 1) / BLK * BLK;
-  const int jb = t.j0 + min(t.jcount, (piece * WAVES + w) * per);
+  const int jb = t.j0 + (SPLIT ? min(t.jcount, (piece * WAVES + w) * per) : w * per);
   const int je = min(t.j0 + t.jcount, jb + per);
   // the tile may hold more than 64 targets (its width follows the forward pair
   // kernel's shape): walk it in chunks of one target per lane
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_coulomb_vjp(const TileDev *__res
         sy = fma(inv3, py_ - t3 * dy, sy);
         sz = fma(inv3, pz_ - t3 * dz, sz);
       };
-      if (n == BLK) {
+      if (UNROLL && n == BLK) {
 #pragma unroll 4
         for (int jj = 0; jj < BLK; ++jj) body(rec[j0 + jj]);
       } else {
@@ -580,7 +580,7 @@ void launch_coulomb_vjp(const State<Real> &st, const Phys &ph, const AdjState<Re
   if constexpr (sizeof(Real) == 8) {
     // the forward's pieces (where there are several): smaller workgroups spread better
     if (ph.pair_parts > 1) {
-      hipLaunchKernelGGL((k_coulomb_vjp<Real, 4, B, true>), dim3(n_tiles * ph.pair_parts), dim3(256), 0, s, st.tiles,
+      hipLaunchKernelGGL((k_coulomb_vjp<Real, 4, B, true, true>), dim3(n_tiles * ph.pair_parts), dim3(256), 0, s, st.tiles,
                          ad.rec, st.jr, ad.xc[0], ad.xc[1], ad.xc[2], Real(ph.near2), Real(ph.inv_ux), n_tiles,
                          ph.pair_parts, ph.N, st.part);
       hipLaunchKernelGGL(k_vjp_parts, grid_n<Real>(ph.N), dim3(256), 0, s, ph.N, ph.pair_parts, ph.inv_ux, st.part,
@@ -588,9 +588,17 @@ void launch_coulomb_vjp(const State<Real> &st, const Phys &ph, const AdjState<Re
       return;
     }
   }
-  hipLaunchKernelGGL((k_coulomb_vjp<Real, W, B, false>), dim3(n_tiles), dim3(64 * W), 0, s, st.tiles, ad.rec, st.jr,
-                     ad.xc[0], ad.xc[1], ad.xc[2], Real(ph.near2), Real(ph.inv_ux), n_tiles, 1, ph.N,
-                     (double *)nullptr);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(n_tiles), dim3(64 * W), 0, s, st.tiles, ad.rec, st.jr, ad.xc[0], ad.xc[1], ad.xc[2],
+                       Real(ph.near2), Real(ph.inv_ux), n_tiles, 1, ph.N, (double *)nullptr);
+  };
+  // Unrolled, a wave has four sources on their way, which only pays while no second workgroup shares the CU, and
+  // in FP64.  Eight reverse steps in FP32, rolled and unrolled, us: 12,000 particles (188 tiles) 2,230 and 1,870; 16,000
+  // (250) 2,510 and 2,210; 20,000 (313) 3,810 and 4,133; 40,000 9,250 and 10,408.
+  if (sizeof(Real) == 8 || n_tiles <= 256)
+    go(k_coulomb_vjp<Real, W, B, false, true>);
+  else
+    go(k_coulomb_vjp<Real, W, B, false, false>);
 }
 template <class Real>
 void launch_short_range_vjp(const State<Real> &st, const Phys &ph, const AdjState<Real> &ad, int n_cells, int mode,

@@ -146,6 +146,18 @@ def simulation(sizes, real_bytes=4, p3m=None, reorder=0, cfg=None, graph=True, *
     seed()
     return ctx
 
+def adjoint(ctx, steps=2, ckpt=1):
+    """Names of the kernels of a gradient."""
+    size = C.c_size_t()
+    ctx.check(ctx._L.depo_adjoint_workspace_bytes(ctx._h, steps, ckpt, C.byref(size)), "size")
+    work = np.zeros(size.value + 256, np.uint8)
+    s = len(ctx.sp)
+    w, g = np.ones(s), np.zeros((s, 3))
+    fake.fake_reset()
+    ctx.check(ctx._L.depo_adjoint(ctx._h, steps, ckpt, depo._dptr(w), depo._dptr(g), (work.ctypes.data + 255) // 256 * 256,
+                                  size.value, None), "adjoint")
+    return ran()
+
 def ran():
     """Names of the kernels that ran since the last reset, in order."""
     return [fake.fake_name(i).decode() for i in range(fake.fake_ran())]

@@ -408,3 +408,21 @@ def test_fp32_symmetric_adjoint_shapes_on_uneven_samples(cfg):
         dev = (np.abs(g["this"] - g[key])[big] / np.abs(g[key])[big]).max()
         say("against", key, dev, g["this"].tolist())
         assert dev < tol
+
+
+@pytest.mark.parametrize("n", [16384, 16449])
+def test_fp32_one_sided_adjoint_on_both_sides_of_a_workgroup_per_cu(n):
+    """The one-sided pair adjoint takes another loop beyond 256 tiles of 64 targets (ragged last ones): charges and
+    tolerance as in the test of the symmetric shapes, against the symmetric adjoint."""
+    from paper_2205_04979_amd.depo import PAIR_KAHAN, PAIR_SYMMETRIC
+    p, f, x, d, q, off, sp, v0 = sensitive_case(n_per=n, S=1)
+    p = dict(p, collide=False, vdw=False, wall_image=False)
+    say("case: one-sided adjoint", n)
+    g = []
+    for cfg, mode in (((4, 1, 64), PAIR_SYMMETRIC), ((1, 8, 32), PAIR_KAHAN)):
+        sim = gpu_sim(p, f, off, 4)
+        sim.set_kernel_config(*cfg, mode=mode)
+        sim.seed(sp, x, d, 30.0 * q, v=v0)
+        g.append(sim.adjoint(4, 2)[0, 0])
+    say(g)
+    assert g[0] != 0 and abs(g[1] - g[0]) < 1e-5 * abs(g[0])

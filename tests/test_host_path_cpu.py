@@ -98,3 +98,13 @@ print(json.dumps([out, builds()]))
     want = [17, 0] if fused else [0, 17]
     assert got[0] in ([want], [want, [0, 17], [17, 0], want]), got
     assert got[1] == ([17, 0] if sum(sizes) <= 131072 else [0, 17]), got
+
+
+@pytest.mark.parametrize("n,kernel", [(16384, "Lb0ELb1E"), (16385, "Lb0ELb0E")])
+def test_the_one_sided_adjoint_unrolls_up_to_a_workgroup_per_cu(tmp_path, n, kernel):
+    """Up to 256 tiles the loop over the sources of the FP32 adjoint is unrolled, beyond it is not."""
+    got = run(tmp_path, f"""
+s = simulation([{n}], cfg=(1, 8, 32, 1), soft_tally=True)
+print(json.dumps([k for k in adjoint(s) if "13k_coulomb_vjpI" in k]))
+""")
+    assert len(got) == 2 and all(f"k_coulomb_vjpIfLi16ELi32E{kernel}" in k for k in got), got
