@@ -249,7 +249,8 @@ enum {
  * that prefetches source records one group ahead.  The symmetric mode takes
  * block = 64 (sources are paired in rounds of 64) and items of
  * 64 * targets_per_lane * waves >= 256 targets, at most 2^22 of them per
- * layout (DEPO_E_INVALID beyond). */
+ * layout (DEPO_E_INVALID beyond).  The FP32 pair adjoint takes the symmetric
+ * shape too, (8, 1) as (4, 2) and always with float records. */
 depo_status depo_set_kernel_config(depo_ctx *ctx, int32_t targets_per_lane, int32_t waves, int32_t block,
                                    int32_t mode, int32_t use_graph);
 

@@ -360,8 +360,11 @@ void launch_coulomb_vjp_sym(const State<float> &st, const Phys &ph, const AdjSta
   double *ax = reinterpret_cast<double *>(st.accx);
   double *ay = reinterpret_cast<double *>(st.accy);
   double *az = reinterpret_cast<double *>(st.accz);
-  // The forward's items fix the tile.  Four targets per lane as there, except where its layout took fewer
-  // (sizes as there).
+  // The forward's items fix the tile, and they are cut for its waves: the adjoint takes its targets per lane, where
+  // those fewer than four fill the chip with more waves (eight reverse steps of four samples of 12,000
+  // particles at (1, 8): 2,865 us, 4,183 as (4, 2); of one of 30,000 at (2, 4) 3,330, 3,930 as (4, 2)).
+  // Eight per lane are more registers than the sums and products leave: (8, 1) runs as (4, 2) (two of 20,000
+  // 8,900 -> 5,600 us with the forward steps).
   auto go = [&](auto kernel, int threads) {
     if (n_items > 0)
       hipLaunchKernelGGL(kernel, dim3(n_items), dim3(threads), 0, s, st.items, ad.rec, st.jr, ax, ay, az,
@@ -373,7 +376,11 @@ void launch_coulomb_vjp_sym(const State<float> &st, const Phys &ph, const AdjSta
       else if (cfg.ipl == 2) go(k_coulomb_vjp_sym<2, 2>, 128);
       else go(k_coulomb_vjp_sym<4, 1>, 64);
       break;
-    case 512: go(k_coulomb_vjp_sym<4, 2>, 128); break;
+    case 512:
+      if (cfg.ipl == 1) go(k_coulomb_vjp_sym<1, 8>, 512);
+      else if (cfg.ipl == 2) go(k_coulomb_vjp_sym<2, 4>, 256);
+      else go(k_coulomb_vjp_sym<4, 2>, 128);
+      break;
     default: go(k_coulomb_vjp_sym<4, 4>, 256); break;   // 1,024
   }
   if (ph.N > 0)

@@ -426,3 +426,9 @@ def test_fp32_one_sided_adjoint_on_both_sides_of_a_workgroup_per_cu(n):
         g.append(sim.adjoint(4, 2)[0, 0])
     say(g)
     assert g[0] != 0 and abs(g[1] - g[0]) < 1e-5 * abs(g[0])
+
+
+@pytest.mark.parametrize("cfg", [(1, 8, 64), (2, 4, 64), (8, 1, 64)])
+def test_fp32_symmetric_adjoint_of_wide_tiles_on_uneven_samples(cfg):
+    """The shapes of 512 targets a tile, as the others."""
+    test_fp32_symmetric_adjoint_shapes_on_uneven_samples(cfg)

@@ -108,3 +108,18 @@ s = simulation([{n}], cfg=(1, 8, 32, 1), soft_tally=True)
 print(json.dumps([k for k in adjoint(s) if "13k_coulomb_vjpI" in k]))
 """)
     assert len(got) == 2 and all(f"k_coulomb_vjpIfLi16ELi32E{kernel}" in k for k in got), got
+
+
+@pytest.mark.parametrize("ipl,waves,runs", [(1, 4, (1, 4)), (1, 8, (1, 8)), (2, 2, (2, 2)), (2, 4, (2, 4)), (4, 1, (4, 1)),
+                                            (4, 2, (4, 2)), (4, 4, (4, 4)), (8, 1, (4, 2))])
+def test_the_symmetric_adjoint_runs_in_the_shape_that_was_chosen(tmp_path, ipl, waves, runs):
+    """Every shape of the symmetric pair kernel is the adjoint's too, in both record formats, but that of eight
+    targets per lane."""
+    got = run(tmp_path, f"""
+out = []
+for mode in (2, 4):
+    s = simulation([3000], cfg=({ipl}, {waves}, 64, mode), soft_tally=True)
+    out += [k for k in adjoint(s) if "k_coulomb_vjp_sym" in k]
+print(json.dumps(out))
+""")
+    assert len(got) == 4 and all(f"k_coulomb_vjp_symILi{runs[0]}ELi{runs[1]}E" in k for k in got), got
