@@ -228,20 +228,26 @@ __device__ __forceinline__ void ring_item(const SymItem &it, const JSrc<float> *
       }
       if constexpr (REACT) {
         // as in ring_round4 (18,000 particles, two targets per lane: 93 -> 87 us; raised for the root
-        // too it gains nothing here)
-        __builtin_amdgcn_s_setprio(1);
+        // too it gains nothing here; with four and more per lane it only loses: see below)
+        if constexpr (IPL <= 2) __builtin_amdgcn_s_setprio(1);
         rx = dpp<kWaveRol1>(rx);
         ry = dpp<kWaveRol1>(ry);
         rz = dpp<kWaveRol1>(rz);
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (IPL <= 2) __builtin_amdgcn_s_setprio(0);
       }
     };
     if constexpr (REACT && IPL == 4 && !INTREC) {
       // LDS addresses are the low 32 bits of a generic pointer into it
       nearmask = ring_round4((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) JSrc<float> *)rs, xi, yi, zi,
                              qi, near2, sx, sy, sz, rx, ry, rz);
-    } else if constexpr (REACT) {
+    } else if constexpr (REACT && IPL <= 2) {
 #pragma unroll 4
+      for (int t = 0; t < 64; ++t) step(t, -1);
+    } else if constexpr (REACT) {
+      // The integer records' four targets per lane, and eight: two steps at a time and no raised priority.  2^20
+      // particles in integer records at (4, 4): 255.6 ms with four steps and the priority raised, 245.1 with four, 237.7
+      // so; 65,536 at (4, 1) 1,075, 1,027, 1,001 us, at (8, 1) 1,249 with both, 1,046 with four.
+#pragma unroll 2
       for (int t = 0; t < 64; ++t) step(t, -1);
     } else {
       // wave-uniform; outside [0, IPL) when no self pair
