@@ -9,6 +9,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -369,9 +370,12 @@ CoulombConfig default_sym(const std::vector<int64_t> &off) {
 // waves for four rounds an item, half of the sources after a tile go in pieces of sixteen: they start first
 // and spare additions to the accumulators, the short ones level the end (ten samples of 2,048 to
 // 32,768 particles 728 -> 703 us, 65,536 769 -> 760 us; three quarters in long pieces: 714 and 775 us).
+// The tile of an item off the diagonal is whole, so its cost is its length: the many of those are counted by
+// length and written where they belong (a comparison sort of the list took most of a seed: 500,000 particles
+// 172 ms sorted, 51 so, on one host).
 constexpr int64_t kLongPiece = 64 * 16;
-void build_items(const depo_ctx *ctx, int T, int rounds, std::vector<SymItem> &items) {
-  std::vector<SymItem> diag, off;
+int64_t build_items(const depo_ctx *ctx, int T, int rounds, std::unique_ptr<SymItem[]> &items) {
+  std::vector<SymItem> diag;
   const int64_t P = 64 * (int64_t)rounds, Pd = std::min<int64_t>(P, T);
   for (int s = 0; s < ctx->S; ++s) {
     const int64_t e = ctx->off[s + 1];
@@ -379,30 +383,46 @@ void build_items(const depo_ctx *ctx, int T, int rounds, std::vector<SymItem> &i
       const int64_t own = std::min<int64_t>(T, e - b);
       for (int64_t p = 0; p < own; p += Pd)
         diag.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)(b + p), (int32_t)std::min(Pd, own - p), s, 1, {0, 0}});
-      int64_t j = b + own;
-      for (int64_t k = rounds == 4 ? (e - j) / (2 * kLongPiece) : 0; k > 0; --k, j += kLongPiece)
-        off.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)j, (int32_t)kLongPiece, s, 0, {0, 0}});
-      for (; j < e; j += P)
-        off.push_back(SymItem{(int32_t)b, (int32_t)own, (int32_t)j, (int32_t)std::min(P, e - j), s, 0, {0, 0}});
     }
   }
-  auto by_cost = [](const SymItem &a, const SymItem &c) {
+  std::stable_sort(diag.begin(), diag.end(), [](const SymItem &a, const SymItem &c) {
     return (int64_t)a.icount * a.jcount > (int64_t)c.icount * c.jcount;
+  });
+  // f(sample, tile, sources from, their number) for every item off the diagonal
+  auto each = [&](auto &&f) {
+    for (int s = 0; s < ctx->S; ++s) {
+      const int64_t e = ctx->off[s + 1];
+      for (int64_t b = ctx->off[s]; b + T < e; b += T) {
+        int64_t j = b + T;
+        for (int64_t k = rounds == 4 ? (e - j) / (2 * kLongPiece) : 0; k > 0; --k, j += kLongPiece) f(s, b, j, kLongPiece);
+        for (; j < e; j += P) f(s, b, j, std::min(P, e - j));
+      }
+    }
   };
-  std::stable_sort(diag.begin(), diag.end(), by_cost);
-  std::stable_sort(off.begin(), off.end(), by_cost);
-  items = diag;
-  items.insert(items.end(), off.begin(), off.end());
+  std::vector<int64_t> at(std::max(P, kLongPiece) + 1, 0);   // items of a length; then the next one's place
+  each([&](int, int64_t, int64_t, int64_t n) { ++at[n]; });
+  int64_t total = (int64_t)diag.size();
+  for (int64_t n = (int64_t)at.size() - 1; n >= 0; --n) {
+    const int64_t here = at[n];
+    at[n] = total;
+    total += here;
+  }
+  items.reset(new SymItem[total]);
+  std::copy(diag.begin(), diag.end(), items.get());
+  each([&](int s, int64_t b, int64_t j, int64_t n) {
+    items[at[n]++] = SymItem{(int32_t)b, (int32_t)T, (int32_t)j, (int32_t)n, s, 0, {0, 0}};
+  });
+  return total;
 }
 
 // Upload the symmetric work items for the current configuration.
 depo_status upload_items(depo_ctx *ctx) {
-  std::vector<SymItem> items;
+  std::unique_ptr<SymItem[]> items;
   const int T = coulomb_sym_tile(ctx->ccfg);
-  build_items(ctx, T, sym_rounds(ctx, T, ctx->ccfg.waves), items);
-  if ((int64_t)items.size() > ctx->sym_cap) return ctx->fail(DEPO_E_CAPACITY, "symmetric item list exceeds capacity");
-  ctx->n_items = (int)items.size();
-  if (!items.empty()) HIP_TRY(hipMemcpy(ctx->sf.items, items.data(), items.size() * sizeof(SymItem), hipMemcpyHostToDevice));
+  const int64_t n = build_items(ctx, T, sym_rounds(ctx, T, ctx->ccfg.waves), items);
+  if (n > ctx->sym_cap) return ctx->fail(DEPO_E_CAPACITY, "symmetric item list exceeds capacity");
+  ctx->n_items = (int)n;
+  if (n) HIP_TRY(hipMemcpy(ctx->sf.items, items.get(), n * sizeof(SymItem), hipMemcpyHostToDevice));
   return DEPO_OK;
 }
 

@@ -61,7 +61,11 @@ int hipGetLastError(void) { int e = last; last = OK; return e; }
 const char *hipGetErrorString(int e) { return e ? "failed on request" : "no error"; }
 int hipGetDevice(int *d) { *d = 0; return OK; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; *p = aligned_alloc(256, (size_t)64 << 20); return OK; }
-int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memcpy(d, s, n); return OK; }
+static void *copy_at; static size_t copy_bytes;
+/* the last synchronous copy */
+void *fake_copy_at(void) { return copy_at; }
+size_t fake_copy_bytes(void) { return copy_bytes; }
+int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; copy_at = d; copy_bytes = n; memcpy(d, s, n); return OK; }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)k; (void)st; memcpy(d, s, n); return OK; }
 int hipStreamCreateWithFlags(void **s, unsigned f) { (void)f; *s = malloc(1); return OK; }
 int hipStreamDestroy(void *s) { free(s); return OK; }
@@ -145,6 +149,16 @@ def simulation(sizes, real_bytes=4, p3m=None, reorder=0, cfg=None, graph=True, *
     ctx.steps_done = steps_done
     seed()
     return ctx
+
+fake.fake_copy_at.restype = C.c_void_p
+fake.fake_copy_bytes.restype = C.c_size_t
+
+def items(ctx, *cfg):
+    """The work items of the symmetric pair kernel in a shape (the call's last copy): target, number of targets, source,
+    number of sources, sample, diagonal."""
+    ctx.check(ctx._L.depo_set_kernel_config(ctx._h, *cfg, 64, 2, 1), "shape")
+    n = fake.fake_copy_bytes() // 4
+    return np.ctypeslib.as_array(C.cast(fake.fake_copy_at(), C.POINTER(C.c_int32)), (n,)).reshape(-1, 8)[:, :6].copy()
 
 def adjoint(ctx, steps=2, ckpt=1):
     """Names of the kernels of a gradient."""

@@ -123,3 +123,55 @@ for mode in (2, 4):
 print(json.dumps(out))
 """)
     assert len(got) == 4 and all(f"k_coulomb_vjp_symILi{runs[0]}ELi{runs[1]}E" in k for k in got), got
+
+
+@pytest.mark.parametrize("sizes", [(1, 63, 0, 64, 65, 255, 256, 257, 511, 513, 1, 2049), (9000,), (17, 21000, 5000)])
+@pytest.mark.parametrize("shape", [(1, 4), (2, 2), (4, 1), (1, 8), (2, 4), (4, 2), (8, 1), (4, 4)])
+def test_the_items_of_the_symmetric_kernel_hold_every_pair_once(tmp_path, sizes, shape):
+    """Blocks of 64 x 64 of each sample's pairs: those of a tile with itself on the diagonal items, those with all later
+    sources on the others, each exactly once; diagonal items first, either kind by cost."""
+    got = run(tmp_path, f"""
+sizes = {sizes}
+t = items(simulation(sizes), *{shape})
+T = 64 * {shape[0]} * {shape[1]}
+off = np.concatenate([[0], np.cumsum(sizes)])
+ok = [True] * 5
+for s, (b, e) in enumerate(zip(off[:-1], off[1:])):
+    m = t[t[:, 4] == s]
+    n = e - b
+    seen = np.zeros(((n + 63) // 64, (n + 63) // 64), int)
+    for i0, ni, j0, nj, _, diag in m:
+        ok[0] &= bool((i0 - b) % T == 0 and ni == min(T, e - i0) and (j0 - b) % 64 == 0 and 0 < nj <= e - j0)
+        ok[1] &= bool(j0 + nj <= i0 + ni and j0 >= i0 if diag else j0 >= i0 + T)
+        ok[2] &= bool(nj % 64 == 0 or j0 + nj == e or (diag and j0 + nj == i0 + ni))
+        seen[(i0 - b) // 64:(i0 - b + ni + 63) // 64, (j0 - b) // 64:(j0 - b + nj + 63) // 64] += 1
+    c = np.arange(len(seen)) * 64 // T
+    ok[3] &= bool((seen == (c[None, :] >= c[:, None])).all())
+cost = t[:, 1].astype(np.int64) * t[:, 3]
+k = int(t[:, 5].sum())
+ok[4] = bool(t[:k, 5].all() and (np.diff(cost[:k]) <= 0).all() and (np.diff(cost[k:]) <= 0).all())
+print(json.dumps(ok))
+""")
+    assert all(got), got
+
+
+def test_the_item_list_is_written_not_sorted(tmp_path):
+    """The list of 262,144 particles in tiles of 256 takes three to four times as long as to copy it (24 to
+    26 times when it was sorted by comparisons; bound 10)."""
+    got = run(tmp_path, """
+import time
+s = simulation([262144])
+def best(f):
+    out = []
+    for _ in range(7):
+        t = time.perf_counter()
+        f()
+        out.append(time.perf_counter() - t)
+    return min(out)
+t = items(s, 4, 1)
+a = np.zeros((len(t), 8), np.int32)
+b = np.zeros_like(a)
+print(json.dumps([len(t), best(lambda: s._L.depo_set_kernel_config(s._h, 4, 1, 64, 2, 1)), best(lambda: np.copyto(b, a))]))
+""")
+    print(got)
+    assert got[1] < 10 * got[2], got
