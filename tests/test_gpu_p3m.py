@@ -376,3 +376,27 @@ def test_p3m_longest_lines(fine, coarse, alpha_h):
     say("FP32 against FP64", e.max(), "against the coarse mesh", rel_rms(a["64"], a["coarse"]))
     assert np.all(e <= p3m_fp32_bound(w, nearest_distance(ora, tg)))
     assert rel_rms(a["64"], a["coarse"]) < 1e-2
+
+
+@pytest.mark.parametrize("real_bytes", [8, 4])
+@pytest.mark.parametrize("reorder", [0, 3])
+def test_p3m_batched_steps_equal_single_ones(real_bytes, reorder):
+    """P3M under graphs of four steps, in calls on both sides of every batch length, with a storage reorder on steps
+    inside and between the batches or none: bitwise the state of single direct steps."""
+    from paper_2205_04979_amd.depo import PAIR_P3M, Simulation
+    w = make_workload("single-65k", n=3000, field_n=32)
+    f = w.field()
+    out = []
+    for graph, calls in ((True, (5, 15, 16, 1, 21, 4, 32)), (False, (1,) * 94)):
+        sim = Simulation(w.params, w.offsets, f.shape[:3], real_bytes=real_bytes,
+                         p3m=dict(mesh_x=64, mesh_yz=32, alpha_h=0.5, rmax_alpha=3.5))
+        sim.init_field(f)
+        sim.set_kernel_config(1, 1, 1, mode=PAIR_P3M, use_graph=graph)
+        sim.set_reorder(reorder)
+        sim.seed(w.sample_params, w.x, w.d, w.qbase)
+        for c in calls:
+            sim.step(c)
+        out.append(sim.read())
+    say("case: p3m batched steps, reorder", reorder, "fp", 8 * real_bytes)
+    for k in ("x", "v", "a", "dep_step", "neighbours"):
+        assert np.array_equal(out[0][k], out[1][k]), k

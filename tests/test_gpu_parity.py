@@ -1034,3 +1034,71 @@ def test_eight_targets_per_lane_keep_up_with_two_in_integer_records():
             best[k] = min(best[k], time.perf_counter() - t)
     say("case: integer records, (8, 1) and (2, 2), ms", [1e3 * b for b in best])
     assert best[0] < 1.15 * best[1]
+
+
+def test_batched_steps_of_a_layout_with_the_general_cell_build():
+    """Beyond 131,072 particles the kernel of a step's second half and the next one's first half fills the histogram
+    that the list's last pass cleared earlier in the same graph: 17 steps by graphs of four and one against 17
+    direct ones, bitwise, with contacts and with removals at the wall."""
+    n = 131100
+    w = make_workload("single-65k", n=n, field_n=32)
+    f = w.field()
+    x, d = w.x.copy(), w.d
+    rng = np.random.default_rng(3)
+    er = rng.normal(size=(40, 2))
+    er /= np.linalg.norm(er, axis=1)[:, None]
+    x[:40, 1:] = er * (w.params["R"] - 0.5 * d[:40] - rng.uniform(0.0, 2e-6, 40))[:, None]
+    for k in range(100, 4000, 2):
+        x[k + 1] = x[k] + [0.9 * 0.5 * (d[k] + d[k + 1]), 0.0, 0.0]
+    x[:, 0] = np.mod(x[:, 0], w.params["L"])
+    v0 = np.zeros((n, 3))
+    v0[:40, 1:] = 0.5 * er
+    say("case: batched steps, general cell build")
+    out = []
+    for graph, calls in ((True, (17,)), (False, (1,) * 17)):
+        sim, _ = seeded_pair(w.params, f, x, d, w.qbase, w.offsets, w.sample_params, 4, v0=v0, oracle=False)
+        sim.set_kernel_config(4, 1, 64, 2, use_graph=graph)
+        for c in calls:
+            sim.step(c)
+        out.append((sim.read(), sim.tally()))
+    assert (out[0][0]["dep_step"] > 0).any() and out[0][0]["neighbours"].any()
+    for k in ("x", "v", "a", "dep_step", "neighbours"):
+        assert np.array_equal(out[0][0][k], out[1][0][k]), k
+    assert out[0][1] == out[1][1]
+
+
+def test_symmetric_default_of_more_particles_than_512_target_tiles_allow():
+    """A single sample beyond 1.48 million particles takes the symmetric kernel by default, in tiles of 1,024 (it took
+    the one-sided one before): forces of 2,000 targets against FP64 sums over all particles and against the
+    one-sided kernel, relative to the sum of the pairs' sizes (1e-5, as at every size)."""
+    import torch
+    n = 1500000
+    w = make_workload("large-1m", n=n, field_n=32)
+    p = dict(w.params, collide=False, vdw=False, wall_image=False, wall_vdw=False, drag=False)
+    say("case: symmetric default at 1.5 million")
+    sim, _ = seeded_pair(p, w.field(), w.x, w.d, w.qbase, w.offsets, w.sample_params, 4, oracle=False)
+    sim.eval_accel()
+    g = sim.read()
+    sim.set_kernel_config(1, 8, 32, 1)
+    sim.eval_accel()
+    one = sim.read()["a"]
+    tg = np.unique(np.concatenate([[0, 1, 1023, 1024, n - 1, n - 865], np.random.default_rng(2).integers(0, n, 2000)]))
+    q = torch.from_numpy(w.sample_params[0, 0] * w.qbase).cuda()
+    x, d = torch.from_numpy(g["x"]).cuda(), torch.from_numpy(w.d).cuda()
+    m = p["rho_p"] * np.pi * w.d ** 3 / 6
+    k_e = 1.0 / (4 * np.pi * p["eps0"])
+    worst = [0.0, 0.0]
+    for t in tg:
+        r = x[t] - x
+        r[:, 0] -= p["L"] * torch.round(r[:, 0] / p["L"])
+        dist = torch.linalg.norm(r, dim=1)
+        c = q / torch.maximum(dist, 0.5 * (d[t] + d)) ** 2
+        c[t] = 0.0
+        dist[t] = 1.0
+        f = k_e * float(q[t]) / m[t]
+        ref = f * torch.sum((c / dist)[:, None] * r, dim=0).cpu().numpy()
+        scale = abs(f) * float(torch.sum(torch.abs(c)))
+        for k, a in enumerate((g["a"][t], one[t])):
+            worst[k] = max(worst[k], np.linalg.norm(a - ref) / scale)
+    say("targets", tg.size, "symmetric", worst[0], "one-sided", worst[1])
+    assert worst[0] < 1e-5 and worst[1] < 1e-5
