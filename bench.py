@@ -550,6 +550,20 @@ def p3m_run(steps: int = 5, names=None) -> dict:
     return out
 
 
+def choose_shape(sim, kernel: str, tuned: bool):
+    """Set the pair-kernel shape that the headline leg runs with, and return it with the autotuner's times (None
+    where it did not run): the one given, the autotuner's choice, or (4, 1, 64, 2)."""
+    if not kernel and tuned:
+        from paper_2205_04979_amd.autotune import autotune
+        shape, tune = autotune(sim, steps=10)
+        log(f"[bench] autotuned pair kernel (ms per step): {shape} " +
+            ", ".join(f"{k}:{v:.3f}ms" for k, v in tune.items()))
+        return shape, tune
+    shape = tuple(int(v) for v in kernel.split(",")) if kernel else (4, 1, 64, 2)
+    sim.set_kernel_config(*shape)
+    return shape, None
+
+
 def main():
     global REORDER
     ap = argparse.ArgumentParser()
@@ -641,17 +655,7 @@ def main():
     sim = Simulation(w.params, w.offsets, field.shape[:3], real_bytes=4, device="cuda:0")
     sim.init_field(field)
     sim.seed(w.sample_params, w.x, w.d, w.qbase)
-    tune = None
-    if args.kernel:
-        sim.set_kernel_config(*[int(v) for v in args.kernel.split(",")])
-        shape = tuple(int(v) for v in args.kernel.split(","))
-    elif not args.no_autotune:
-        from paper_2205_04979_amd.autotune import autotune
-        shape, tune = autotune(sim, steps=10)
-        log(f"[bench] autotuned pair kernel (ms per step): {shape} " +
-            ", ".join(f"{k}:{v:.3f}ms" for k, v in tune.items()))
-    else:
-        shape = (4, 2, 64, 2)          # the library default in FP32
+    shape, tune = choose_shape(sim, args.kernel, not args.no_autotune)
     if args.copy_probe_mb:
         src = torch.empty(args.copy_probe_mb << 20, dtype=torch.uint8, device="cuda:0").fill_(1)
         dst = torch.empty_like(src)

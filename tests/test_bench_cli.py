@@ -15,3 +15,23 @@ def test_bench_refuses_more_than_one_gpu():
     assert r.returncode == 2
     line = json.loads(r.stdout.strip().splitlines()[-1])
     assert line["n_gpus"] == 2 and "one GPU" in line["error"]
+
+
+def test_the_shape_that_bench_reports_is_the_one_it_set():
+    """Without the autotuner the headline leg reports a shape that the simulation was given."""
+    if ROOT not in sys.path:
+        sys.path.insert(0, ROOT)
+    import bench
+
+    class Sim:
+        def __init__(self):
+            self.calls = []
+
+        def set_kernel_config(self, *shape):
+            self.calls.append(shape)
+
+    for kernel in (None, "1,8,32", "4,4,64,2"):
+        sim = Sim()
+        shape, tune = bench.choose_shape(sim, kernel, False)
+        assert sim.calls == [shape] and tune is None
+        assert kernel is None or shape == tuple(int(v) for v in kernel.split(","))
