@@ -244,20 +244,8 @@ __device__ __forceinline__ double sdiff(uint64_t a, uint64_t b) {
 // exact integer differences of the fixed-point positions plus the difference of their
 // remainders (dr*, in quanta).  The gap is formed as (|r|^2 - s^2) / (|r| + s): near contact it
 // is a small fraction of |r|, and the plain difference |r| - s would lose most of its digits.
-template <class Pos>
-__device__ __forceinline__ double pair_gap(Pos xi, Pos yi, Pos zi, Pos xj, Pos yj, Pos zj, double drx, double dry,
-                                           double drz, double ux, double ur, double s, double &dx, double &dy,
-                                           double &dz, double &dist) {
-  dx = ((double)as_signed(Pos(xi - xj)) + drx) * ux;
-  dy = ((double)as_signed(Pos(yi - yj)) + dry) * ur;
-  dz = ((double)as_signed(Pos(zi - zj)) + drz) * ur;
-  const double r2 = dx * dx + dy * dy + dz * dz;
-  dist = sqrt(r2);
-  return (r2 - s * s) / (dist + s);
-}
-
-// The gap of pair_gap where it is at most `most`; where it surely is more (the squared distance says so
-// with a margin far above rounding), any larger value, without the root and the division.
+// Where the gap surely is more than `most` (the squared distance says so with a margin far above
+// rounding), it comes back infinite, without the root and the division.
 template <class Pos>
 __device__ __forceinline__ double pair_gap_within(double most, Pos xi, Pos yi, Pos zi, Pos xj, Pos yj, Pos zj,
                                                   double drx, double dry, double drz, double ux, double ur, double s,
