@@ -343,7 +343,8 @@ int64_t count_tile_items(const std::vector<int64_t> &off, int64_t T) { return co
 // with 4 rounds, 789 with 2 (33 thousand waves with 4); 45,000 393 and 407 (16 thousand); 30,000 214
 // and 205 (7 thousand); 14,000 at (2, 2) 62.7 with 2, 68.4 with 1 (6 thousand waves with 2); 9,000 at
 // (1, 4) 42.9 and 41.5 (4.9 thousand); 3,001 20.9 and 17.9.  So 4 rounds from 12 waves per SIMD on, 2 from 5 on.
-// A layout whose item list would not fit takes whole tiles.
+// A layout whose item list would not fit takes whole tiles, and so does every default of (4, 4): its room is that of
+// whole tiles of 512 or 1,024, and with four rounds an item 2^20 particles would take 202.7 ms instead of 199.0.
 int sym_rounds(const depo_ctx *ctx, int T, int waves) {
   auto fits = [&](int r) { return count_items(ctx->off, T, r) <= ctx->sym_cap; };
   auto per_simd = [&](int r) { return (double)count_items(ctx->off, T, r) * waves / kSimds; };
@@ -357,6 +358,9 @@ int sym_rounds(const depo_ctx *ctx, int T, int waves) {
 // 64): pair sums of one sample, us, with 1, 2 and 4 targets per lane: 7,000 particles (6 thousand blocks)
 // 30.5, 42.5, 61; 11,000 (15 thousand) 47, 53, 70; 14,000 (24 thousand) 64.8, 62.7, 78.6; 18,000 (40
 // thousand) 96, 93.5, 98.6; 24,000 (70 thousand) 160, 153, 137; 65,536 (524 thousand) 1,084, 1,012, 766.
+// Four targets per lane in one, two and four waves, whole steps, us: 40,000 particles 345, 342, 342; 65,536 818, 825, 822;
+// ten samples of 2,048 to 32,768 536, 542, 545; 64 of 17,000 3,677, 3,779, 3,732; a gradient of eight steps of 16
+// samples of 16,384 20,030, 20,760, 21,340.
 // Tiles of 256 targets, or of 1,024 where 256 would make too many items (2^20 particles: 192 ms).
 CoulombConfig default_sym(const std::vector<int64_t> &off) {
   if (count_tile_items(off, 256) > kMaxItems) return CoulombConfig{4, 4, 64, true, true};
@@ -473,7 +477,8 @@ bool short_range_on(const depo_ctx *ctx) { return (ctx->p.flags & (DEPO_COLLIDE 
 // Whether a captured step has two branches: they pay where the pair sums take far longer than their join and fork
 // (the P3M pipeline has cell passes of its own: one branch).  Steps in FP32 with one and with two branches, us:
 // 1,024 particles 28.6, 30.9; 3,001 33.9, 34.2; 4,000 (2,016 blocks of pairs) 38.0, 36.6; 5,600 42.7, 39.6;
-// 16,000 106, 97; in FP64 the same way.
+// 16,000 93.5, 89.2; 65,536 824, 819; 131,072 3,241, 3,235; ten samples of 2,048 to 32,768 558, 535.  In FP64 9,000
+// 107, 103; 65,536 3,114, 3,090.
 bool forks(const depo_ctx *ctx) {
   return short_range_on(ctx) && (ctx->p.flags & DEPO_COULOMB) && !ctx->p3m_use &&
          count_items(ctx->off, 64, 1) > kForkBlocks;
