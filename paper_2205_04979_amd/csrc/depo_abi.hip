@@ -602,14 +602,6 @@ template <class Real> depo_status capture_steps(depo_ctx *ctx, int steps, hipGra
   return DEPO_OK;
 }
 
-// Whether long calls take the batch graph.  With two branches and a storage reorder between the steps, whose halves
-// then stay apart, it saves the gaps between graphs only, which a larger layout hides (128 steps in fours and
-// one by one, us: 4,500 particles 7,288 and 7,468; 9,000 8,634 and 8,767; 16,000 14,618 and 14,373; 30,000
-// 29,876 and 29,707).
-bool batch_pays(const depo_ctx *ctx) {
-  return !(forks(ctx) && reorders(ctx) && count_items(ctx->off, 64, 1) > 20000);
-}
-
 template <class Real> depo_status run_steps(depo_ctx *ctx, int n, hipStream_t s) {
   if (n == 0) return DEPO_OK;
   auto replay = [&](hipGraphExec_t x, int steps, int times) -> depo_status {
@@ -627,7 +619,7 @@ template <class Real> depo_status run_steps(depo_ctx *ctx, int n, hipStream_t s)
     return e;
   };
   const int end = ctx->nstep + n;
-  const bool batches = n >= kBatchFrom && batch_pays(ctx);
+  const bool batches = n >= kBatchFrom;
   // The first graph of a call is captured before its first launch: a call that cannot capture it leaves the state
   // and the step counters as they were.  A second one it can do without.
   if (!ctx->gexec && !ctx->gexec_batch) {
