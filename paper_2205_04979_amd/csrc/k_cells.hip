@@ -5,9 +5,10 @@
 // counts -> scatter with per-cell atomic slots -> per-cell ascending sort of
 // the particle indices, so the neighbour walk and hence every force sum runs
 // in a fixed order (bitwise reproducible).  The sort pass also clears the
-// counts for the next build, so no memset is ever enqueued.  These five short
-// launches cost more than their work below some ten thousand particles; there
-// k_cells_fused builds the same list alone, without the histogram.
+// counts for the next build, so no memset is ever enqueued.  Up to 131,072
+// particles k_cells_fused, one launch for these five and the histogram, builds the
+// same list (below a hundred thousand it is the faster one by itself), but not on a
+// branch beside a one-sided pair kernel.
 #include "common.hpp"
 #include "launch.hpp"
 

@@ -17,9 +17,9 @@
 // wave, lane = class, runs the two short chains; the others take one node and class per lane, one
 // chunk ahead of the chains and one behind, with one barrier per chunk.  With few classes the
 // speed chain bounds the time (about 17 dependent operations a node), with many the FP64 rate.
-// One lane per class, each marching alone through every node, took 1.48 ms for 480 classes x
-// 1,600 nodes and 1.56 ms for 25,920 (0.4 waves per SIMD, every latency exposed); now 0.18 and
-// 0.44 ms.  Error of the result against 80-bit arithmetic over 1,000 random classes: relative rms
+// One lane per class, each marching alone through every node, took 1.61 ms for 480 classes x
+// 1,600 nodes and 1.62 ms for 25,920 (0.4 waves per SIMD, every latency exposed); now 0.18 and
+// 0.46 ms.  Error of the result against 80-bit arithmetic over 1,000 random classes: relative rms
 // 1.00e-15, as with the library's pow, exp, expm1, sqrt and divisions (1.00e-15).
 //
 // Closures (the paper defers them to other publications; these are stated
@@ -360,10 +360,10 @@ void launch_lf(const LfConst &c, int64_t n, const double *d, const double *q, co
                hipStream_t s) {
   if (n <= 0) return;
   // The fewer classes a workgroup takes, the more of the chip a small call uses, until there are more
-  // workgroups than CUs: 16 up to 4,096 classes (a workgroup per CU; 168 us at 3,000 classes x 1,600
-  // nodes, 212 with 32, 264 with 64), 32 up to 8,192 (220 us at 8,000; 344 with 16, 268 with 64), then
-  // 64, where the node waves' lanes all share a node and the chains' wave is full (437 us at 25,920;
-  // 567 with 32).
+  // workgroups than CUs: 16 up to 4,096 classes (a workgroup per CU; 172 us at 3,000 classes x 1,600
+  // nodes, 213 with 32, 279 with 64), 32 up to 8,192 (225 us at 8,000; 333 with 16, 278 with 64), then
+  // 64, where the node waves' lanes all share a node and the chains' wave is full (460 us at 25,920;
+  // 572 with 32).
   auto go = [&](auto kernel, int C) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)((n + C - 1) / C)), dim3(kLfThreads), 0, s, c, n, d, q, A, out);
   };
